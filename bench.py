@@ -283,7 +283,7 @@ def main():
         ref_match_ms, ref_gather_ms, _ = A.avsg_timing(op_ref.h, args.steps)
         ref_after = op_ref.stats()
         op_ref.close()
-        ref_host = ref_after["host_bytes"] - ref_before["host_bytes"]
+        ref_host = gather_host_bytes({k: ref_after[k] - ref_before[k] for k in ref_after}, sum(spec.row_bytes))
         ref_gsec = float(np.sum(ref_gather_ms)) * 1e-3
         ref_gbps = ref_host / ref_gsec / 1e9 if ref_gsec > 0 else 0.0
         s3_block = (_traffic_block(TRAFFIC_SUMMARY_S3)
@@ -299,7 +299,8 @@ def main():
                                   "frac_of_hipmemcpy_peak": round(ref_gbps / memcpy_peak, 4) if memcpy_peak else None,
                                   "algorithmic_bytes_per_launch": round(ref_host / args.steps),
                                   "traffic": None, "traffic_source": None,
-                                  "what": "every miss's row bytes over the host link / the S3 kernel's "
+                                  "what": "row bytes of every miss that the S3 kernel reads from the host "
+                                          "(rows staged while Stage One ran are not among them) / its "
                                           "average duration (HIP events on the step stream)"}}
         if s3_block:
             reference["roofline"]["traffic"] = s3_block["traffic_bytes_per_launch"]
@@ -351,7 +352,10 @@ def main():
         step_ms = step_ms + np.nan_to_num(np.asarray(tail_ms[:n_step], dtype=np.float64))
     gather_s = float(np.sum(gather_ms)) * 1e-3
     match_s = float(np.sum(match_ms)) * 1e-3
-    gather_gbps = host_moved / gather_s / 1e9 if gather_s > 0 and host_moved else 0.0
+    # the gather's own host reads: rows that the matching launch read into
+    # staging while Stage One ran are not among them
+    gather_host = gather_host_bytes({k: after[k] - before[k] for k in after}, row_total) if host_moved else 0
+    gather_gbps = gather_host / gather_s / 1e9 if gather_s > 0 else 0.0
     eff_gbps = host_moved / wall / 1e9 if host_moved else 0.0
 
     # ---- CPU baseline: the oracle on the same inputs ----
@@ -411,6 +415,8 @@ def main():
                                          - before["lost_exhausted"] - before["lost_collision"]) / K, 1),
         "misses_per_step": round(misses / K, 1),
         "host_rows_per_step": round(host_moved / row_total / K, 1) if row_total else 0.0,
+        # of those, rows read while Stage One ran
+        "staged_rows_per_step": round((host_moved - gather_host) / row_total / K, 1) if row_total else 0.0,
         # resident reuse: misses filled from another slot of the request, and
         # same-step repeats (written by their index's host copy or copied after)
         "resident_rows_per_step": round((after["resident_rows"] - before["resident_rows"]) / K, 1),
@@ -457,7 +463,7 @@ def main():
                                                / traffic["algorithmic_traffic_bytes_per_launch"], 3)
                                          if traffic and traffic.get("algorithmic_traffic_bytes_per_launch")
                                          else None),
-            "algorithmic_bytes_per_launch": round(host_moved / K) if host_moved else 0,
+            "algorithmic_bytes_per_launch": round(gather_host / K),
             # what the host link itself carried per launch (128-byte lines,
             # per the counters) and its rate over the same launches
             "host_link_bytes_per_launch": traffic.get("host_read_bytes_per_launch") if traffic else None,
@@ -531,6 +537,8 @@ def _measure(spec, gather_mode, X, N, ptrs, ctx, warm, timed, dev):
             op.close()
         d = {k: after[k] - before[k] for k in ("hits", "lookups", "misses", "host_bytes")}
         if events:
+            res["gather_host_bytes"] = gather_host_bytes({k: after[k] - before[k] for k in after},
+                                                         sum(spec.row_bytes))
             if d != res["delta"]:
                 raise RuntimeError(f"{spec.name}: the timed pass with events differs from the plain pass")
             stage_two = np.asarray(gather_ms, dtype=np.float64) + np.asarray(tail_ms, dtype=np.float64)
@@ -582,7 +590,7 @@ def config_block(memcpy_peak, dev, warm=8, timed=32, with_cpu=True):
                 m = _measure(spec, gm, X, N, ptrs, wl.ctx, warm, timed, dev)
                 d = m["delta"]
                 gsec = float(np.sum(m["stage_two_ms"])) * 1e-3
-                gbps = d["host_bytes"] / gsec / 1e9 if gsec > 0 and d["host_bytes"] else 0.0
+                gbps = m["gather_host_bytes"] / gsec / 1e9 if gsec > 0 else 0.0
                 pre = "" if label == "default" else label + "_"
                 entry[pre + "us_per_step"] = round(m["wall"] / timed * 1e6, 2)
                 entry[pre + "match_us_median"] = round(float(np.median(m["match_ms"])) * 1e3, 2)
@@ -693,11 +701,11 @@ def access_shape_probe(out_path, warm=4, timed=16):
         d = m["delta"]
         gsec = float(np.sum(m["stage_two_ms"])) * 1e-3
         misses = d["misses"]
-        line_bytes = misses * 128 * sum(lines(rb) for rb in row_bytes)
+        line_bytes = m["gather_host_bytes"] // sum(row_bytes) * 128 * sum(lines(rb) for rb in row_bytes)
         row = {"layout": label, "row_bytes": list(row_bytes), "batch": 16, "topk": 2048,
                "misses_per_step": round(misses / timed, 1),
                "gather_us_median": round(float(np.median(m["stage_two_ms"])) * 1e3, 2),
-               "payload_gbps": round(d["host_bytes"] / gsec / 1e9, 3),
+               "payload_gbps": round(m["gather_host_bytes"] / gsec / 1e9, 3),
                "line_gbps": round(line_bytes / gsec / 1e9, 3),
                "line_frac_of_hipmemcpy_peak": round(line_bytes / gsec / 1e9 / peak, 4)}
         results.append(row)
@@ -747,7 +755,7 @@ def appendix_d_sweep(out_path):
                 after = op.stats()
                 op.close()
                 misses = after["misses"] - before["misses"]
-                moved = misses * W.KV_ROW_BYTES
+                moved = gather_host_bytes({k: after[k] - before[k] for k in after}, W.KV_ROW_BYTES)
                 gsec = float(np.sum(gather_ms)) * 1e-3
                 row = {"batch": B, "reuse_target": reuse, "strategy": name,
                        "hit_rate": round((after["hits"] - before["hits"]) /
@@ -1156,7 +1164,7 @@ def config_table(out_path):
                 # the list kernel, then matching beside the early copies, then
                 # the finishing kernel: all of it is Stage Two's launches
                 gather_ms, match_ms = gather_ms + match_ms, None
-            moved = d["host_bytes"]
+            moved = gather_host_bytes(d, sum(spec.row_bytes))
             gsec = float(np.sum(gather_ms)) * 1e-3
             row = {"workload": name, "strategy": label, "batch": spec.batch, "topk": spec.topk,
                    "slots": run_spec.slots, "n_q": spec.n_q,
@@ -1194,9 +1202,19 @@ def config_table(out_path):
 # sources that decide the profiled kernel's traffic: the gather code and the
 # matching code that plans which rows it reads
 GATHER_SOURCES = ("paper_2609_37538_amd/csrc/gather.hip", "paper_2609_37538_amd/csrc/gather_body.h",
-                  "paper_2609_37538_amd/csrc/match_body.h", "paper_2609_37538_amd/csrc/avsg_internal.h")
+                  "paper_2609_37538_amd/csrc/match_body.h", "paper_2609_37538_amd/csrc/avsg_internal.h",
+                  "paper_2609_37538_amd/csrc/fetch_body.h")
 TRAFFIC_SUMMARY = "profiles/gather_resident_traffic_batch64_mtp2.md"
 TRAFFIC_SUMMARY_S3 = "profiles/gather_balanced_traffic_batch64_mtp2.md"
+
+
+def gather_host_bytes(d, row_total):
+    """Host-link payload of the Stage Two kernels over a counter delta: all of
+    it but the rows that the matching launch read into staging while Stage One
+    ran (the early-fetch transfer, which has a list of early rows, reads its
+    staged rows in the launch that is timed)."""
+    staged = 0 if d["early_rows"] else d["early_staged_rows"]
+    return d["host_bytes"] - staged * row_total
 
 
 def measured_traffic(args, gather_name):

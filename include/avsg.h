@@ -155,7 +155,9 @@ typedef struct avsg_stats_t {
     uint64_t copy_calls;      /* AVSG_GATHER_SDMA: runtime copy calls issued (one per step when the HIP
                                  runtime in the process has the batched copy call, else one per row) */
     uint64_t early_rows;      /* AVSG_GATHER_EARLY: host rows fetched before Stage One (one per index) */
-    uint64_t early_staged_rows;   /* of those, rows parked in staging until their slots were known */
+    uint64_t early_staged_rows;   /* of those, rows parked in staging until their slots were known;
+                                     AVSG_GATHER_RESIDENT and _BALANCED: host rows read into staging
+                                     while Stage One ran (timing decides which, not what a step leaves) */
     uint64_t early_deferred_rows; /* of those, rows read after Stage One because staging was full */
 } avsg_stats_t;
 
@@ -176,7 +178,7 @@ avsg_status avsg_resolve_config(const avsg_config *cfg, avsg_config *out);
 
 /* A call of this library's own with no counterpart in the paper (which keeps
  * the table in each core's on-chip buffer): size in bytes of the device
- * workspace that avsg_create needs for cfg
+ * workspace of cfg
  * (per-request tables of 8*S bytes, transfer lists of 8*N_q*K bytes, a hit
  * mask of N_q*K bytes, counters and pointer tables; with AVSG_GATHER_RESIDENT
  * or AVSG_GATHER_EARLY three more lists of 8*N_q*K bytes and fan slot pairs
@@ -184,8 +186,13 @@ avsg_status avsg_resolve_config(const avsg_config *cfg, avsg_config *out);
  * with AVSG_GATHER_EARLY also early keys, positions and finish entries of
  * 36*N_q*K bytes per request and the staging rows (early_staging_rows, by
  * default min(B*N_q*K, 16384), times the row bytes of every stream); with
- * AVSG_GATHER_PIPELINED a chunk queue of 16 bytes per 32 misses).  Returns 0
- * for an invalid cfg. */
+ * AVSG_GATHER_PIPELINED a chunk queue of 16 bytes per 32 misses; at the end,
+ * with hash matching, up to 224 requests and at least 512 indices per request
+ * and step, at most 2.5 MB of staging rows and tables
+ * for the host rows that AVSG_GATHER_RESIDENT and AVSG_GATHER_BALANCED read
+ * while Stage One runs: avsg_create also takes a workspace without that part
+ * and then reads every host row after Stage One).  Returns 0 for an invalid
+ * cfg. */
 size_t avsg_workspace_bytes(const avsg_config *cfg);
 
 /* Create a handle and reset every table to empty (c_j = -1, lifetime -1, every
@@ -355,8 +362,8 @@ avsg_status avsg_destroy(avsg_handle *h);
  * _NONE, and dual-pointer matching with _BALANCED, _REQUEST or _NONE.
  * Errors: AVSG_E_INVAL (null pointer, misaligned rows, a continuing call after
  * another configuration or a failed call), AVSG_E_NOTPOW2, AVSG_E_RANGE,
- * AVSG_E_CAPACITY (avsg_workspace_bytes(cfg) above AVSG_STATIC_SCRATCH_BYTES,
- * or the LDS limit), AVSG_E_UNSUPPORTED (validate mode or another transfer),
+ * AVSG_E_CAPACITY (the workspace without its staging rows above
+ * AVSG_STATIC_SCRATCH_BYTES, or the LDS limit), AVSG_E_UNSUPPORTED (validate mode or another transfer),
  * AVSG_E_HIP; each error is described on stderr. */
 avsg_status avsg_step_static(const avsg_config *cfg, const void *const *host_rows,
                              const int64_t *rows_per_request, void *const *d_buffers,

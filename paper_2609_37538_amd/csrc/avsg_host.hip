@@ -52,6 +52,7 @@ struct avsg_handle {
   int stage_rows = 0;
   int early_workers = 0;
   size_t early_list_lds = 0;
+  AheadView ahead{};            // rows fetched while Stage One runs (served = 0: none)
   int* pipe_ctl = nullptr;      // head, tail, done, exit_count, error, last epoch
   int4* pipe_chunks = nullptr;
   int pipe_max_chunks = 0;
@@ -101,6 +102,14 @@ constexpr size_t kLdsPerWorkgroup = 160 * 1024;   // gfx950
 constexpr int kRepeatWorkersPerCu = 4;
 constexpr int kEarlyStagingRows = 16384;   // default staging capacity of the early-fetch transfer
 constexpr int kEarlyWorkers = 32;          // default copy workgroups beside the matching ones
+constexpr int kAheadWorkgroups = 32;       // look-ahead fetch: workgroups beside the matching ones
+constexpr int kAheadCus = 256;             // CUs of the GPU: the fetch is off when they are not left over
+constexpr int64_t kAheadMinLookups = 512;  // indices per request and step below which it is off
+constexpr int64_t kAheadBytes = 256 << 10; // link bytes fetched per step, plus as many per query token
+constexpr int64_t kAheadBytesPerToken = 256 << 10;
+constexpr int kAheadMaxTokens = 8;         // tokens that count
+constexpr int kAheadMaxRows = 64;          // rows of one workgroup
+constexpr int kAheadMaxEntries = 256;      // table entries of one workgroup
 
 size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -117,6 +126,7 @@ size_t pipe_chunks_for(const avsg_config& c);
 struct Layout {
   size_t table_c, table_q, miss_list, hit_mask, plan, early, pipe, pipe_bytes, stats, host_ptrs, buf_ptrs,
       rows, val, total;
+  size_t ahead_table, ahead_rows0, ahead_rows1, with_ahead;   // past `total`: used when the workspace holds it
 };
 
 bool has_plan(const avsg_config& c) {
@@ -149,6 +159,31 @@ std::array<size_t, 9> early_sections(const avsg_config& c) {
   return off;
 }
 
+// Look-ahead fetch (fetch_body.h) of a configuration: workgroups, rows and
+// tables, without addresses (every hash transfer's workspace has its section;
+// the transfers that take their host rows from a list use it).  It is off where a request looks up fewer than 512 indices
+// per step: Stage One is then over before the first row could arrive (one
+// request, us per step without and with it: K = 256 11.2 / 11.7, K = 512 12.9
+// / 12.7, K = 1024 15.1 / 14.3, K = 256 with four tokens 17.9 / 16.7).
+AheadView ahead_of(const avsg_config& c) {
+  AheadView a{};
+  if (c.match_mode != AVSG_MATCH_HASH || static_cast<int64_t>(c.n_q) * c.topk < kAheadMinLookups ||
+      c.batch + kAheadWorkgroups > kAheadCus)
+    return a;
+  int64_t line_bytes = 0;   // of one row of every stream: the link carries whole lines
+  for (int s = 0; s < c.n_streams; ++s) line_bytes += (c.row_bytes[s] + 127) / 128 * 128;
+  const int64_t budget = kAheadBytes + kAheadBytesPerToken * std::min(c.n_q, kAheadMaxTokens);
+  const int parts = std::max(1, kAheadWorkgroups / c.batch), served = std::min(c.batch, kAheadWorkgroups);
+  const int64_t quota = std::min<int64_t>(kAheadMaxRows, budget / (served * parts) / line_bytes);
+  if (quota < 1) return a;   // a row beyond a workgroup's share
+  a.parts = parts;
+  a.served = served;
+  a.quota = static_cast<int>(quota);
+  a.entries = 64;           // at most a quarter full, so few indices lose their entry to another
+  while (a.entries < kAheadMaxEntries && a.entries < 4 * a.quota) a.entries *= 2;
+  return a;
+}
+
 Layout layout_of(const avsg_config& c) {
   Layout L{};
   const size_t B = static_cast<size_t>(c.batch), S = static_cast<size_t>(c.slots);
@@ -172,6 +207,13 @@ Layout layout_of(const avsg_config& c) {
   L.val = off;
   if (c.validate) off += up(B * static_cast<size_t>(c.n_q) * 4);
   L.total = off;
+  const AheadView a = ahead_of(c);
+  const size_t wgs = static_cast<size_t>(a.served) * a.parts;
+  L.ahead_table = off; off += up(wgs * a.entries * 8);
+  L.ahead_rows0 = off; off += up(wgs * a.quota * static_cast<size_t>(c.row_bytes[0]));
+  L.ahead_rows1 = off;
+  if (c.n_streams > 1) off += up(wgs * a.quota * static_cast<size_t>(c.row_bytes[1]));
+  L.with_ahead = off;
   return L;
 }
 
@@ -287,8 +329,10 @@ avsg_status hip_fail(avsg_handle* h, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail((h), e_, #call); \
   } while (0)
 
-// Section pointers of a workspace laid out by layout_of(h->cfg) at ws.
-void bind_workspace(avsg_handle* h, unsigned char* ws, const Layout& L) {
+// Section pointers of a workspace of `bytes` bytes laid out by layout_of(h->cfg)
+// at ws.  The look-ahead fetch runs when the workspace holds its section and
+// the GPU has CUs for its workgroups beside the matching ones.
+void bind_workspace(avsg_handle* h, unsigned char* ws, const Layout& L, size_t bytes, int cus) {
   const avsg_config& c = h->cfg;
   const int B = c.batch;
   h->table_c = reinterpret_cast<int32_t*>(ws + L.table_c);
@@ -330,6 +374,15 @@ void bind_workspace(avsg_handle* h, unsigned char* ws, const Layout& L) {
   h->buf_ptrs = reinterpret_cast<uint64_t*>(ws + L.buf_ptrs);
   h->rows_dev = reinterpret_cast<int64_t*>(ws + L.rows);
   h->val_rows = c.validate ? reinterpret_cast<int32_t*>(ws + L.val) : nullptr;
+  h->ahead = AheadView{};
+  const AheadView a = ahead_of(c);
+  const bool list_transfer = c.gather_mode == AVSG_GATHER_RESIDENT || c.gather_mode == AVSG_GATHER_BALANCED;
+  if (list_transfer && a.served > 0 && bytes >= L.with_ahead && c.batch + a.served * a.parts <= cus) {
+    h->ahead = a;
+    h->ahead.table = reinterpret_cast<int2*>(ws + L.ahead_table);
+    h->ahead.stage0 = reinterpret_cast<uint64_t>(ws + L.ahead_rows0);
+    h->ahead.stage1 = c.n_streams > 1 ? reinterpret_cast<uint64_t>(ws + L.ahead_rows1) : 0;
+  }
 }
 
 // Request sizes, and host-row and buffer addresses aligned for the copies.
@@ -367,7 +420,7 @@ avsg_status avsg_check_config(const avsg_config* cfg) { return check_config(cfg,
 
 size_t avsg_workspace_bytes(const avsg_config* cfg) {
   if (check_config(cfg, nullptr) != AVSG_OK) return 0;
-  return layout_of(resolved(*cfg)).total;
+  return layout_of(resolved(*cfg)).with_ahead;
 }
 
 avsg_status avsg_resolve_config(const avsg_config* cfg, avsg_config* out) {
@@ -425,7 +478,9 @@ avsg_status avsg_create(const avsg_config* cfg, const void* const* host_rows,
     return AVSG_E_HIP;
   }
   h->m = log2_exact(c.slots);
-  bind_workspace(h, static_cast<unsigned char*>(d_workspace), L);
+  const int cus = device_cus();
+  h->cus = cus;
+  bind_workspace(h, static_cast<unsigned char*>(d_workspace), L, workspace_bytes, cus);
   if (c.validate) h->h_val.resize(static_cast<size_t>(B) * c.n_q);
   h->rows.assign(rows_per_request, rows_per_request + B);
   h->host_dev.resize(static_cast<size_t>(c.n_streams) * B);
@@ -442,8 +497,6 @@ avsg_status avsg_create(const avsg_config* cfg, const void* const* host_rows,
     h->host_dev[i] = reinterpret_cast<uint64_t>(dptr);
     h->bufs[i] = reinterpret_cast<uint64_t>(d_buffers[i]);
   }
-  const int cus = device_cus();
-  h->cus = cus;
   h->workers = c.gather_workers > 0 ? c.gather_workers : std::max(1, cus);
 
   auto cleanup = [&](avsg_status rc) {
@@ -455,6 +508,7 @@ avsg_status avsg_create(const avsg_config* cfg, const void* const* host_rows,
   hipError_t e;
   if (c.match_mode == AVSG_MATCH_HASH) {
     h->lds = stage_one_lds_bytes(c.slots, c.topk, c.n_q, has_plan(c));
+    if (h->ahead.served > 0) h->lds = std::max(h->lds, ahead_lds_bytes(c.slots, h->ahead.entries, h->ahead.quota));
     int max_lds = 0;
     if ((e = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device)) !=
         hipSuccess)
@@ -691,7 +745,12 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
       p.plan_counts = h->plan_counts;
       p.plan_claim = h->plan_claim;
     }
-    HIP_TRY(h, launch_match_hash(p, h->lds, s));
+    AheadParams a{};
+    a.view = h->ahead;
+    a.n_streams = c.n_streams; a.host_ptrs = h->host_ptrs;
+    a.row_bytes0 = c.row_bytes[0];
+    a.row_bytes1 = c.n_streams > 1 ? c.row_bytes[1] : 0;
+    HIP_TRY(h, launch_match_hash(p, a, h->lds, s));
   } else {
     DualPtrParams p{};
     p.B = c.batch; p.K = c.topk; p.topk = d_topk; p.rows = h->rows_dev; p.state = h->dp_state;
@@ -708,6 +767,7 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
   g.row_bytes0 = c.row_bytes[0];
   g.row_bytes1 = c.n_streams > 1 ? c.row_bytes[1] : 0;
   g.topk = d_topk; g.slots = d_slots; g.hit_mask = h->hit_mask;
+  g.ahead = h->ahead;
   switch (c.gather_mode) {
     case AVSG_GATHER_BALANCED: HIP_TRY(h, launch_gather_balanced(g, h->workers, s)); break;
     case AVSG_GATHER_REQUEST: HIP_TRY(h, launch_gather_request(g, s)); break;
@@ -1160,14 +1220,15 @@ extern "C" avsg_status avsg_step_static(const avsg_config* cfg, const void* cons
   h.cfg = c;
   h.device = dev;
   h.m = log2_exact(c.slots);
-  bind_workspace(&h, sd.ptr, L);
   h.cus = device_cus();
+  bind_workspace(&h, sd.ptr, L, AVSG_STATIC_SCRATCH_BYTES, h.cus);
   h.workers = c.gather_workers > 0 ? c.gather_workers : std::max(1, h.cus);
   int max_lds = 0;
   if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
     return AVSG_E_HIP;
   if (c.match_mode == AVSG_MATCH_HASH) {
     h.lds = stage_one_lds_bytes(c.slots, c.topk, c.n_q, has_plan(c));
+    if (h.ahead.served > 0) h.lds = std::max(h.lds, ahead_lds_bytes(c.slots, h.ahead.entries, h.ahead.quota));
     if (max_lds > 0 && h.lds > static_cast<size_t>(max_lds)) return AVSG_E_CAPACITY;
     if (sd.match_lds < h.lds) {
       if (prepare_match_hash(h.lds) != hipSuccess) return AVSG_E_HIP;

@@ -29,7 +29,8 @@ enum StatIndex : int {
   kStatResident,
   kStatDuplicate,
   kStatEarly,          // rows fetched before Stage One (early-fetch transfer)
-  kStatEarlyStaged,    // of those, rows parked in HBM staging until their slots were known
+  kStatEarlyStaged,    // rows parked in HBM staging until their slots were known (early-fetch transfer: of
+                       // those; look-ahead fetch: all of its rows)
   kStatEarlyDeferred,  // of those, rows read from the host only after Stage One (staging full)
   kNumStats
 };
@@ -68,6 +69,24 @@ struct MatchParams {
   uint32_t* early_done;         // [B] 1 once the request's slots are written
 };
 
+// Host rows that the matching launch reads into HBM staging ahead of the
+// gather (fetch_body.h): one small table per fetching workgroup.
+struct AheadView {
+  int32_t served;               // requests [0, served) are fetched for (0: no row is fetched ahead)
+  int32_t parts;                // fetching workgroups per request
+  int32_t quota;                // rows a workgroup fetches at most
+  int32_t entries;              // entries of a workgroup's table, a power of two, at most 256
+  int2* table;                  // [served * parts][entries] (index, its place among the workgroup's rows; -1 = none)
+  uint64_t stage0, stage1;      // [served * parts][quota] staged rows of each stream
+};
+
+struct AheadParams {
+  AheadView view;
+  int32_t n_streams;
+  const uint64_t* host_ptrs;    // [n_streams][B]
+  int64_t row_bytes0, row_bytes1;
+};
+
 struct GatherParams {
   int32_t B, n_q, K, S;
   // entry counts of request r: miss_counts[r * count_stride + g], g < counts_per_req
@@ -84,6 +103,7 @@ struct GatherParams {
   const int32_t* topk;          // [B][n_q][K]
   const int32_t* slots;         // [B][n_q][K]
   const uint8_t* hit_mask;      // [B][n_q][K]
+  AheadView ahead;              // rows already in HBM staging (served = 0: none)
 };
 
 // Device-wide chunk queue of the pipelined step (workspace resident).
@@ -147,7 +167,10 @@ size_t match_lds_bytes(int S, int K);
 int match_threads(int S, int K);
 size_t dualptr_lds_bytes(int K);
 
-hipError_t launch_match_hash(const MatchParams& p, size_t lds, hipStream_t s);
+// `ahead`: served * parts further workgroups fetch rows beside the matching ones
+hipError_t launch_match_hash(const MatchParams& p, const AheadParams& ahead, size_t lds, hipStream_t s);
+// dynamic LDS of a fetching workgroup
+size_t ahead_lds_bytes(int S, int entries, int quota);
 hipError_t prepare_match_hash(size_t lds);
 hipError_t launch_reset_tables(int32_t* c, uint32_t* q, size_t n, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long* p, size_t n, hipStream_t s);

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "avsg_internal.h"
+#include "fetch_body.h"
 
 namespace avsg {
 namespace {
@@ -230,8 +231,19 @@ __device__ __forceinline__ void copy_range(const GatherParams& p, const long lon
       const int2 e = p.miss_list[at];
       const bool ok = e.x >= 0 && e.y >= 0 && e.y < p.S &&
                       (kDevice ? e.x < p.S : static_cast<int64_t>(e.x) < p.rows[r]);
-      const uint64_t base0 = kDevice ? p.buf_ptrs[r] : p.host_ptrs[r];
-      src0[i] = ok ? base0 + static_cast<uint64_t>(e.x) * p.row_bytes0 : 0;
+      uint64_t from0 = kDevice ? p.buf_ptrs[r] : p.host_ptrs[r];
+      uint64_t row = static_cast<uint64_t>(e.x);
+      bool staged = false;
+      if (!kDevice && ok && r < p.ahead.served) {
+        const AheadSpot at = ahead_spot(p.ahead, r, e.x);
+        const int2 f = p.ahead.table[static_cast<size_t>(at.wg) * p.ahead.entries + at.entry];
+        if (f.x == e.x) {   // the row is in HBM already
+          staged = true;
+          from0 = p.ahead.stage0;
+          row = static_cast<uint64_t>(at.wg) * p.ahead.quota + f.y;
+        }
+      }
+      src0[i] = ok ? from0 + row * p.row_bytes0 : 0;
       dst0[i] = p.buf_ptrs[r] + static_cast<uint64_t>(e.y) * p.row_bytes0;
       int2 fan = make_int2(-1, -1);
       if (dstx0) {
@@ -242,8 +254,8 @@ __device__ __forceinline__ void copy_range(const GatherParams& p, const long lon
         dsty0[i] = fan.y >= 0 ? p.buf_ptrs[r] + static_cast<uint64_t>(fan.y) * p.row_bytes0 : 0;
       }
       if (p.n_streams > 1) {
-        const uint64_t base1 = kDevice ? p.buf_ptrs[p.B + r] : p.host_ptrs[p.B + r];
-        src1[i] = ok ? base1 + static_cast<uint64_t>(e.x) * p.row_bytes1 : 0;
+        const uint64_t from1 = kDevice ? p.buf_ptrs[p.B + r] : staged ? p.ahead.stage1 : p.host_ptrs[p.B + r];
+        src1[i] = ok ? from1 + row * p.row_bytes1 : 0;
         dst1[i] = p.buf_ptrs[p.B + r] + static_cast<uint64_t>(e.y) * p.row_bytes1;
         if (dstx1) {
           dstx1[i] = fan.x >= 0 ? p.buf_ptrs[p.B + r] + static_cast<uint64_t>(fan.x) * p.row_bytes1 : 0;

@@ -34,6 +34,7 @@
 // into the write back.  With the resident-reuse gather the workgroup then
 // plans Stage Two (plan_request): which misses need the host link and which
 // can be filled from a slot that already holds their row.
+#include "fetch_body.h"
 #include "match_body.h"
 
 namespace avsg {
@@ -44,8 +45,12 @@ struct NoPublish {
 };
 
 template <int IPT, int NT, int SPT>
-__global__ __launch_bounds__(NT) void match_hash_kernel(MatchParams p) {
+__global__ __launch_bounds__(NT) void match_hash_kernel(MatchParams p, AheadParams a) {
   extern __shared__ __align__(16) unsigned char lds[];
+  if (static_cast<int>(blockIdx.x) >= p.B) {
+    fetch_ahead<NT>(p, a, static_cast<int>(blockIdx.x) - p.B, lds);
+    return;
+  }
   NoPublish none;
   match_request<IPT, NT, SPT>(p, static_cast<int>(blockIdx.x), lds, none);
 }
@@ -306,12 +311,18 @@ hipError_t prepare_match_hash(size_t lds) {
   return hipSuccess;
 }
 
-hipError_t launch_match_hash(const MatchParams& p, size_t lds, hipStream_t s) {
+size_t ahead_lds_bytes(int S, int entries, int quota) {
+  return 4 * (static_cast<size_t>(S) + 2 * static_cast<size_t>(entries) + static_cast<size_t>(quota) + 1);
+}
+
+hipError_t launch_match_hash(const MatchParams& p, const AheadParams& ahead, size_t lds, hipStream_t s) {
   const void* f = match_kernel(p.S, p.K);
   if (!f) return hipErrorInvalidValue;
   MatchParams args = p;
-  void* argv[] = {&args};
-  return hipLaunchKernel(f, dim3(p.B), dim3(match_threads(p.S, p.K)), argv, lds, s);
+  AheadParams aargs = ahead;
+  void* argv[] = {&args, &aargs};
+  const unsigned extra = static_cast<unsigned>(ahead.view.served * ahead.view.parts);
+  return hipLaunchKernel(f, dim3(static_cast<unsigned>(p.B) + extra), dim3(match_threads(p.S, p.K)), argv, lds, s);
 }
 
 hipError_t launch_reset_tables(int32_t* c, uint32_t* q, size_t n, hipStream_t s) {

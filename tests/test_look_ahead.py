@@ -1,0 +1,90 @@
+"""Look-ahead fetch: the matching launch reads some of the step's host rows into
+HBM staging while Stage One runs.  Every output equals the oracle's whichever
+rows it takes, at the edges of the rule that switches it on, of its split of
+requests over workgroups and of its row types."""
+import numpy as np
+import pytest
+
+import oracle as ORC
+import workload as W
+from harness import HostRows, OracleSide, compare_step, log, run_parity_modes
+
+pytestmark = pytest.mark.gpu
+
+BOTH = (0, 6)   # balanced (S3) and resident reuse
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    from paper_2609_37538_amd import avsg as A
+    A.load()
+    W.build(force=False)
+    ORC.build(force=False)
+
+
+CASES = [
+    # name, rows are fetched ahead, kwargs of workload.custom_spec
+    ("at_512_lookups", True, dict(batch=3, topk=256, slots=1024, n_q=2, ctx=6000)),
+    ("at_511_lookups", False, dict(batch=3, topk=511, slots=1024, n_q=1, ctx=6000)),
+    ("one_request", True, dict(batch=1, topk=2048, slots=8192, n_q=1, ctx=60000)),
+    ("ragged", True, dict(batch=7, topk=333, slots=2048, n_q=3, ctx=9001, row_bytes=(580, 132))),
+    ("served_33", True, dict(batch=33, topk=512, slots=1024, n_q=1, ctx=4000, row_bytes=(64, 16))),
+    ("batch_224", True, dict(batch=224, topk=512, slots=512, n_q=1, ctx=1500, row_bytes=(16,))),
+    ("batch_225", False, dict(batch=225, topk=512, slots=512, n_q=1, ctx=1500, row_bytes=(16,))),
+    ("widest_table", True, dict(batch=2, topk=1024, slots=16384, n_q=3, ctx=100000)),
+    ("nine_tokens", True, dict(batch=2, topk=100, slots=1024, n_q=9, ctx=5000, row_bytes=(4,))),
+    ("row_too_long", False, dict(batch=2, topk=512, slots=1024, n_q=1, ctx=1200, row_bytes=(65536,))),
+    ("rewritten_rows", True, dict(batch=2, topk=512, slots=2048, n_q=3, ctx=6000, mode="zipf_window",
+                                  window=64, retention=0.8)),
+]
+
+
+@pytest.mark.parametrize("name,on,kw", CASES, ids=[c[0] for c in CASES])
+def test_look_ahead_parity(name, on, kw):
+    kw = dict(dict(steps=8, retention=0.7), **kw)
+    spec = W.custom_spec(name=f"ahead_{name}", **kw)
+    _, got = run_parity_modes(spec, BOTH, table_every=4, buffers_every=1, miss_list_requests=2, retry=1)
+    rows = sum(spec.row_bytes)
+    for mode in BOTH:
+        assert (got[mode]["early_staged_rows"] > 0) == on, f"mode {mode}"
+        assert got[mode]["early_staged_rows"] <= got[mode]["host_bytes"] // rows
+
+
+@pytest.mark.parametrize("mode", BOTH, ids=["balanced", "resident"])
+def test_workspace_without_staging(mode):
+    """A workspace that lacks the staging section is still taken: every host
+    row is then read after Stage One."""
+    from paper_2609_37538_amd import avsg as A
+    import torch
+    spec = W.custom_spec(name=f"ahead_no_room_{mode}", batch=3, topk=512, slots=2048, n_q=2, steps=6,
+                         ctx=9000, row_bytes=(1152, 132))
+    wl = W.Workload(spec)
+    host = HostRows(wl)
+    orc = OracleSide(wl, host)
+    cfg = A.make_config(spec.batch, spec.topk, spec.n_q, spec.slots, row_bytes=spec.row_bytes, gather_mode=mode)
+    size = A.avsg_workspace_bytes(cfg) - 256
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    bufs = [torch.zeros((spec.batch, spec.slots, rb), dtype=torch.uint8, device="cuda") for rb in spec.row_bytes]
+    slots = torch.empty((spec.batch, spec.n_q, spec.topk), dtype=torch.int32, device="cuda")
+    counts = torch.empty((spec.batch, spec.n_q), dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    h = A.avsg_create(cfg, host.ptrs, wl.ctx, ws.data_ptr(), size,
+                      [b[r].data_ptr() for b in bufs for r in range(spec.batch)], stream)
+    log(f"[gpu] workspace without staging, mode {mode}")
+    try:
+        for t in range(spec.steps):
+            X = wl.topk(t)
+            Xd = torch.from_numpy(np.ascontiguousarray(X, dtype=np.int32)).cuda()
+            A.avsg_step(h, Xd.data_ptr(), None, slots.data_ptr(), counts.data_ptr(), stream)
+            torch.cuda.synchronize()
+            compare_step(t, *orc.step(X, None), slots.cpu().numpy(), counts.cpu().numpy())
+        for s in range(len(spec.row_bytes)):
+            assert np.array_equal(bufs[s].cpu().numpy(), orc.images[s])
+        st = A.avsg_stats(h)
+        assert st["early_staged_rows"] == 0 and st["misses"] > 0
+    finally:
+        A.avsg_destroy(h)
+        host.free()
