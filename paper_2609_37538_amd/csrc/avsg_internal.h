@@ -15,6 +15,36 @@ constexpr int kGatherTile = 64;
 // XCDs of an MI355X (gfx950): 8 accelerator dies of 32 CUs, each with its own L2.
 constexpr int kXcds = 8;
 
+// Loads and stores at a device-visible address held as a number, as global
+// memory accesses: through a plain pointer they become flat ones, which also
+// count as LDS accesses, so that a wave waits for its row loads in flight
+// before each LDS read that follows them.
+template <typename V>
+__device__ __forceinline__ V load_global(uint64_t a) {
+  return *reinterpret_cast<const __attribute__((address_space(1))) V*>(a);
+}
+template <typename V>
+__device__ __forceinline__ void store_global(uint64_t a, V v) {
+  *reinterpret_cast<__attribute__((address_space(1))) V*>(a) = v;
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave, register to register
+// with DPP: shifts by 1, 2, 4 and 8 lanes inside each 16-lane row (a lane
+// whose source lies outside its row adds 0), then the last lane of row 0 is
+// broadcast into row 1 and of row 2 into row 3, and the last lane of row 1
+// (by then the total of rows 0-1) into rows 2 and 3.  Every lane of the wave
+// must be active.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
+  return v;
+}
+
+
 // Per-request device counters (uint64 each, cumulative).
 enum StatIndex : int {
   kStatHits = 0,

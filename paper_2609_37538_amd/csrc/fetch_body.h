@@ -60,8 +60,8 @@ __device__ __forceinline__ void fetch_load(V (&v)[U], const int32_t* list, int t
     const int q = q0 + u * NT;
     if (q < total) {
       const int i = q / chunks, ch = q - i * chunks;
-      v[u] = *reinterpret_cast<const V*>(src + static_cast<uint64_t>(list[i]) * static_cast<uint64_t>(row_bytes) +
-                                         static_cast<uint64_t>(ch) * sizeof(V));
+      v[u] = load_global<V>(src + static_cast<uint64_t>(list[i]) * static_cast<uint64_t>(row_bytes) +
+                            static_cast<uint64_t>(ch) * sizeof(V));
     }
   }
 }
@@ -71,7 +71,7 @@ __device__ __forceinline__ void fetch_store(const V (&v)[U], int total, uint64_t
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int q = q0 + u * NT;
-    if (q < total) *reinterpret_cast<V*>(dst + static_cast<uint64_t>(q) * sizeof(V)) = v[u];
+    if (q < total) store_global<V>(dst + static_cast<uint64_t>(q) * sizeof(V), v[u]);
   }
 }
 template <typename V, int NT, int U>
@@ -109,6 +109,7 @@ __device__ __forceinline__ void fetch_ahead(const MatchParams& p, const AheadPar
 #pragma unroll
   for (int u = 0; u < kPre; ++u) x[u] = tid + u * NT < n ? xg[tid + u * NT] : -1;
   const int64_t rows_r = p.rows[r];
+  const uint64_t src0 = a.host_ptrs[r], src1 = a.n_streams > 1 ? a.host_ptrs[p.B + r] : 0;
   for (int j = tid; j < S / 4; j += NT) reinterpret_cast<fetch_u32x4*>(seen)[j] = 0u;
   for (int j = tid; j < a.view.entries; j += NT) {
     ex[j] = -1;
@@ -145,12 +146,10 @@ __device__ __forceinline__ void fetch_ahead(const MatchParams& p, const AheadPar
   const size_t first = static_cast<size_t>(w) * a.view.quota;
   const uint64_t dst0 = a.view.stage0 + first * static_cast<uint64_t>(a.row_bytes0);
   if (a.n_streams > 1) {
-    const uint64_t src1 = a.host_ptrs[p.B + r];
     const uint64_t dst1 = a.view.stage1 + first * static_cast<uint64_t>(a.row_bytes1);
     if ((a.row_bytes1 & 15) == 0) fetch_copy<fetch_u32x4, NT, 2>(list, m, src1, dst1, a.row_bytes1);
     else fetch_copy<uint32_t, NT, 4>(list, m, src1, dst1, a.row_bytes1);
   }
-  const uint64_t src0 = a.host_ptrs[r];
   if ((a.row_bytes0 & 15) == 0) fetch_copy<fetch_u32x4, NT, 2>(list, m, src0, dst0, a.row_bytes0);
   else fetch_copy<uint32_t, NT, 4>(list, m, src0, dst0, a.row_bytes0);
   for (int j = tid; j < a.view.entries; j += NT)

@@ -35,54 +35,71 @@ __device__ __forceinline__ long long xcd_worker(long long b, long long C) {
 }
 
 __global__ __launch_bounds__(GT) void gather_balanced_kernel(GatherParams p) {
-  __shared__ long long pre[kMaxBatch + 1];
-  __shared__ long long wtot[GT / 64];
+  __shared__ int pre[kMaxBatch + 1], wtot[GT / 64];
   __shared__ uint64_t src0[TILE], dst0[TILE], src1[TILE], dst1[TILE];
   request_prefix(p, pre, wtot);
   const long long N = pre[p.B];
   const long long C = gridDim.x, w = xcd_worker(blockIdx.x, C);
-  const long long a = (w * N) / C;          // Eq. 6: consecutive, floor/ceil(N/C) each
-  const long long b = ((w + 1) * N) / C;
+  const int a = static_cast<int>((w * N) / C);          // Eq. 6: consecutive, floor/ceil(N/C) each
+  const int b = static_cast<int>(((w + 1) * N) / C);
   copy_range<false>(p, pre, a, b, src0, dst0, src1, dst1);
 }
 
 // Resident-reuse Stage Two over two lists: host rows (each also written to
 // its fan slots, the two largest repeats of its index in the step), and rows
-// already in a slot of the same request (not written this step).  The last
-// quarter of the workgroups starts with the resident list and the others
-// with the host list, so the HBM copies run while the host link is busy (the
-// link saturates with far fewer workgroups); each group then moves to the
-// other list.  A host-first workgroup's first tile is a stretch of one
-// request's own host list (first_tiles; none when a request would get more
-// than eight of them), which needs no batch-wide prefix, so
-// host reads start one list read after the launch; the rest of the host list
-// goes in claimed tiles.  Tile i of the resident list first goes to the i-th
-// resident-first workgroup, later tiles are claimed.  Claimed tiles (an atomic
-// counter) let the workgroups that finish first take more (a CU's host-read
-// rate varies up to 2x across the chip; they end the kernel more evenly than a
-// static Eq. 6 split).  A resident list shorter than one full tile per
-// workgroup of its group is cut into tiles of ceil(n / group) rows.
-// claim[0] and claim[1] count the claimed resident and host rows; the
-// matching kernel resets both.
+// already in a slot of the same request (not written this step).  Part of the
+// workgroups starts with the resident list and the others with the host list,
+// so the HBM copies run while the host link is busy (the link saturates with
+// far fewer workgroups); each group then moves to the other list.  From 16
+// requests on half of them start with the resident list, below a quarter: few
+// rows need the many workgroups (11 requests, three tokens: 41.7 against 43.7
+// us with half; one request, four tokens: 37.8 against 39.2), while with many
+// rows fewer host readers leave the other accesses shorter queues (192
+// requests with high reuse 66.3 against 68.7 us, 16 requests 77.3 against
+// 77.7, 32 requests 347.1 against 348.2; 5/8 is no better than half).
+// A host-first workgroup's first tile is a stretch of one request's own host
+// list (first_tiles; none when a request would get more than eight of them),
+// which needs no batch-wide prefix, so host reads start one list read after
+// the launch; without first tiles, tile w of the batch-wide list goes to
+// workgroup w.  Tile i of the resident list first goes to the i-th
+// resident-first workgroup.  Later tiles are claimed (an atomic counter), so
+// the workgroups that finish first take more (a CU's host-read rate varies up
+// to 2x across the chip; they end the kernel more evenly than a static Eq. 6
+// split); a list that the first tiles cover is not claimed from at all (two
+// claims, about 1 us each, at the end of a step with few rows).  A list
+// shorter than one full tile per workgroup of its group is cut into tiles of
+// ceil(n / group) rows.  claim[0] and claim[1] count the claimed resident and
+// host rows; the matching kernel resets both.
+//
+// What bounds it: the host link, which it keeps busy from its first read to
+// its end (16 requests: 61 us for 3.4 MB).  What it can shorten is the chain
+// before that read: launch, counts, list entry with the request's addresses,
+// look-up among the staged rows.  Step before and after batching those reads,
+// 32-bit prefixes by DPP, the unclaimed first tiles and a single row read in
+// flight per thread (see kHostUnroll), us: 16 requests 80.7 -> 77.3; 4
+// requests, two tokens 47.5 -> 45.0; 11 requests, three tokens 45.6 -> 41.7;
+// one request, four tokens 42.8 -> 37.8; 192 requests with high reuse 70.1 ->
+// 66.3; 64 requests, two tokens 509.1 -> 507.4.
 constexpr int kHostTile = 6;
 
 // Rows per tile of a list of n entries shared by `group` workgroups.
-__device__ __forceinline__ int tile_rows(long long n, int group, int max_rows) {
-  const long long t = (n + group - 1) / group;
-  return t < 1 ? 1 : (t > max_rows ? max_rows : static_cast<int>(t));
+__device__ __forceinline__ int tile_rows(int n, int group, int max_rows) {
+  const int t = (n + group - 1) / group;
+  return t < 1 ? 1 : (t > max_rows ? max_rows : t);
 }
 
 // Copy tiles of T entries of a list of n entries: `first` (or none, -1) then
-// claimed tiles, which start at row `base`.
+// claimed tiles, which start at row `base` (none are left to claim, and no
+// claim is made, when that is the list's end).
 template <bool kDevice>
-__device__ void copy_tiles(const GatherParams& p, const long long* pre, long long n, int T, long long first,
-                           long long base, int* counter, long long* next, uint64_t* src0,
-                           uint64_t* dst0, uint64_t* src1, uint64_t* dst1, uint64_t* dstx0 = nullptr,
-                           uint64_t* dstx1 = nullptr, uint64_t* dsty0 = nullptr, uint64_t* dsty1 = nullptr,
-                           const long long* cov = nullptr) {
-  long long t0 = first;
+__device__ void copy_tiles(const GatherParams& p, const int* pre, int n, int T, int first, int base, int* counter,
+                           int* next, uint64_t* src0, uint64_t* dst0, uint64_t* src1, uint64_t* dst1,
+                           uint64_t* dstx0 = nullptr, uint64_t* dstx1 = nullptr, uint64_t* dsty0 = nullptr,
+                           uint64_t* dsty1 = nullptr, const int* cov = nullptr) {
+  int t0 = first;
   for (;;) {
     if (t0 < 0) {
+      if (base >= n) break;
       if (threadIdx.x == 0) *next = base + atomicAdd(counter, T);
       __syncthreads();
       t0 = *next;
@@ -97,48 +114,49 @@ __device__ void copy_tiles(const GatherParams& p, const long long* pre, long lon
 
 __global__ __launch_bounds__(GT) void gather_resident_kernel(GatherParams hp, GatherParams rp,
                                                               int* claim) {
-  __shared__ long long pre_h[kMaxBatch + 1], pre_r[kMaxBatch + 1], cov[kMaxBatch];
-  __shared__ long long wtot[2 * (GT / 64)];
+  __shared__ int pre_h[kMaxBatch + 1], pre_r[kMaxBatch + 1], cov[kMaxBatch];
+  __shared__ int wtot[2 * (GT / 64)];
   __shared__ uint64_t src0[TILE], dst0[TILE], src1[TILE], dst1[TILE], dstx0[TILE], dstx1[TILE], dsty0[TILE],
       dsty1[TILE];
-  __shared__ long long next;
+  __shared__ int next;
   const int C = static_cast<int>(gridDim.x), w = static_cast<int>(blockIdx.x);
-  const int cr = C / 4;                  // workgroups that start with the resident list (may be 0)
-  const int ch = C - cr;                 // >= 1
   const int B = hp.B;
+  const int cr = B >= 16 ? C / 2 : C / 4;   // workgroups that start with the resident list (may be 0)
+  const int ch = C - cr;                 // >= 1
   // the counts of the prefixes below are requested before the first tile, so
   // their latency overlaps it
-  long long ha = 0, hb = 0;
-  if (B <= GT && static_cast<int>(threadIdx.x) < B) {
-    ha = hp.miss_counts[static_cast<size_t>(threadIdx.x) * hp.count_stride];
-    hb = rp.miss_counts[static_cast<size_t>(threadIdx.x) * rp.count_stride];
-  }
-  if (w < ch && first_tiles_on(B, ch)) {
+  const size_t rq = static_cast<int>(threadIdx.x) < B ? threadIdx.x : 0;
+  const int32_t ha = hp.miss_counts[rq * hp.count_stride], hb = rp.miss_counts[rq * rp.count_stride];
+  const bool first_on = first_tiles_on(B, ch);
+  if (w < ch && first_on) {
     // first tile, before any prefix: entries [k T, (k+1) T) of request
     // w mod B's host list, k = w div B (the host link starts one list read
     // after the launch)
     const int r = w % B, k = w / B;
-    const long long cnt = hp.miss_counts[static_cast<size_t>(r) * hp.count_stride];
-    const long long T = first_tile_rows(cnt, first_tiles(r, B, ch), kHostTile);
-    const long long lo = static_cast<long long>(k) * T;
-    const long long hi = lo + T < cnt ? lo + T : cnt;
+    const int cnt = hp.miss_counts[static_cast<size_t>(r) * hp.count_stride];
+    const int T = first_tile_rows(cnt, first_tiles(r, B, ch), kHostTile);
+    const int lo = k * T;
+    const int hi = lo + T < cnt ? lo + T : cnt;
     if (lo < hi)
       copy_range<false>(hp, nullptr, lo, hi, src0, dst0, src1, dst1, dstx0, dstx1, dsty0, dsty1, nullptr, r);
   }
-  // the rest of the host list, batch-wide, in claimed tiles (every group),
-  // and the resident list (tile i of it first to the i-th resident-first
-  // workgroup, the rest claimed)
+  // the rest of the host list, batch-wide (every group; without first tiles
+  // tile w goes first to host-first workgroup w), then claimed tiles, and the
+  // resident list (tile i of it first to the i-th resident-first workgroup,
+  // the rest claimed)
   request_prefix_resid(hp, pre_h, cov, rp, pre_r, wtot, ch, kHostTile, ha, hb);
-  const long long N = pre_h[B], R = pre_r[rp.B];
+  const int N = pre_h[B], R = pre_r[rp.B];
   const int tr = tile_rows(R, cr > 0 ? cr : ch, TILE);
-  const long long res_base = static_cast<long long>(cr) * tr;
+  const int res_base = cr * tr;
+  const int th = first_on ? kHostTile : tile_rows(N, ch, kHostTile);
+  const int host_base = first_on ? 0 : ch * th;
   if (w >= ch) {
-    const long long i = C - 1 - w;       // 0 .. cr-1
+    const int i = C - 1 - w;       // 0 .. cr-1
     copy_tiles<true>(rp, pre_r, R, tr, i * tr, res_base, claim, &next, src0, dst0, src1, dst1);
-    copy_tiles<false>(hp, pre_h, N, kHostTile, -1, 0, claim + 1, &next, src0, dst0, src1, dst1,
+    copy_tiles<false>(hp, pre_h, N, kHostTile, -1, host_base, claim + 1, &next, src0, dst0, src1, dst1,
                       dstx0, dstx1, dsty0, dsty1, cov);
   } else {
-    copy_tiles<false>(hp, pre_h, N, kHostTile, -1, 0, claim + 1, &next, src0, dst0, src1, dst1,
+    copy_tiles<false>(hp, pre_h, N, th, first_on ? -1 : w * th, host_base, claim + 1, &next, src0, dst0, src1, dst1,
                       dstx0, dstx1, dsty0, dsty1, cov);
     copy_tiles<true>(rp, pre_r, R, tr, -1, res_base, claim, &next, src0, dst0, src1, dst1);
   }
@@ -147,14 +165,13 @@ __global__ __launch_bounds__(GT) void gather_resident_kernel(GatherParams hp, Ga
 // Device-to-device row copies (source slot -> slot) over the same balanced
 // split; runs after the host copies of the step, so every source holds its row.
 __global__ __launch_bounds__(GT) void copy_device_kernel(GatherParams p) {
-  __shared__ long long pre[kMaxBatch + 1];
-  __shared__ long long wtot[GT / 64];
+  __shared__ int pre[kMaxBatch + 1], wtot[GT / 64];
   __shared__ uint64_t src0[TILE], dst0[TILE], src1[TILE], dst1[TILE];
   request_prefix(p, pre, wtot);
   const long long N = pre[p.B];
   const long long C = gridDim.x, w = blockIdx.x;
-  const long long a = (w * N) / C;
-  const long long b = ((w + 1) * N) / C;
+  const int a = static_cast<int>((w * N) / C);
+  const int b = static_cast<int>(((w + 1) * N) / C);
   copy_range<true>(p, pre, a, b, src0, dst0, src1, dst1);
 }
 
@@ -186,8 +203,7 @@ __global__ __launch_bounds__(GT) void gather_position_kernel(GatherParams p) {
 }
 
 __global__ __launch_bounds__(GT) void gather_request_kernel(GatherParams p) {
-  __shared__ long long pre[kMaxBatch + 1];
-  __shared__ long long wtot[GT / 64];
+  __shared__ int pre[kMaxBatch + 1], wtot[GT / 64];
   __shared__ uint64_t src0[TILE], dst0[TILE], src1[TILE], dst1[TILE];
   request_prefix(p, pre, wtot);
   const int r = blockIdx.x;                 // Eq. 13: one worker per request

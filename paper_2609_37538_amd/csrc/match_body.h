@@ -28,24 +28,9 @@ __device__ __forceinline__ int bits_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
 }
-// Inclusive prefix sum over the 64 lanes of a wave, register to register
-// with DPP: shifts by 1, 2, 4 and 8 lanes inside each 16-lane row (a lane
-// whose source lies outside its row adds 0), then the last lane of row 0 is
-// broadcast into row 1 and of row 2 into row 3, and the last lane of row 1
-// (by then the total of rows 0-1) into rows 2 and 3.  Every lane of the wave
-// must be active.
-__device__ __forceinline__ int wave_inclusive_scan(int v, int /*lane*/) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
-  return v;
-}
 // Sum over the 64 lanes of a wave, in every lane (every lane active).
 __device__ __forceinline__ int wave_sum(int v) {
-  return __builtin_amdgcn_readlane(wave_inclusive_scan(v, 0), 63);
+  return __builtin_amdgcn_readlane(wave_inclusive_scan(v), 63);
 }
 // Orders this wave's LDS accesses before and after it for the compiler (the
 // hardware runs one wave's LDS instructions in order): lanes that read what
@@ -65,7 +50,7 @@ struct WavePrefix {
 };
 __device__ __forceinline__ WavePrefix wave_prefix(const int* cnt, int nw, int wave) {
   const int lane = lane_id();
-  const int incl = wave_inclusive_scan(lane < nw ? cnt[lane] : 0, lane);
+  const int incl = wave_inclusive_scan(lane < nw ? cnt[lane] : 0);
   WavePrefix r;
   r.total = __builtin_amdgcn_readlane(incl, 63);
   r.before = wave > 0 ? __builtin_amdgcn_readlane(incl, wave - 1) : 0;
@@ -803,7 +788,7 @@ __device__ __forceinline__ void match_request(const MatchParams& p, const int r,
     Own own;
     if (owns) own.load(slife, j0, spt);
     int dcnt = owns ? own.count_below(0, spt) : 0;
-    int incl = wave_inclusive_scan(dcnt, lane);
+    int incl = wave_inclusive_scan(dcnt);
     if (lane == 63) sdead[wave] = incl;
     // prefetch the next token's indices
     if (g + 1 < p.n_q) {
@@ -842,7 +827,7 @@ __device__ __forceinline__ void match_request(const MatchParams& p, const int r,
         }
         step_decays += kstar;
         dcnt = owns ? own.count_below(0, spt) : 0;
-        incl = wave_inclusive_scan(dcnt, lane);
+        incl = wave_inclusive_scan(dcnt);
         if (lane == 63) sdead[wave] = incl;   // every wave read sdead before the loop's barrier
         __syncthreads();
         wbase = wave_prefix(sdead, MW, wave).before;

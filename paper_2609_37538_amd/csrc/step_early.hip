@@ -152,7 +152,7 @@ __global__ __launch_bounds__(NT) void early_list_kernel(EarlyParams e) {
   };
   int mine = 0;
   for (uint32_t h = h0; h < h1; ++h) mine += is_key(h) ? 1 : 0;
-  const int incl = wave_inclusive_scan(mine, lane);
+  const int incl = wave_inclusive_scan(mine);
   if (lane == 63) swc[wave] = incl;
   __syncthreads();
   int idx = incl - mine, total = 0;
