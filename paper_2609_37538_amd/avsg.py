@@ -179,7 +179,7 @@ def _vp(x) -> Optional[ctypes.c_void_p]:
 
 
 def _ptr_array(ptrs: Sequence[int]):
-    return (ctypes.c_void_p * len(ptrs))(*[ctypes.c_void_p(int(p)) for p in ptrs])
+    return (ctypes.c_void_p * len(ptrs))(*map(int, ptrs))
 
 
 def make_config(batch, topk, n_q, slots, retry=3, max_life=16, a1=A1_DEFAULT, a2=A2_DEFAULT,

@@ -1139,6 +1139,7 @@ constexpr int kMaxStaticDevices = 64;
 // Per-GPU state of avsg_step_static (host memory, fixed size).
 struct StaticDevice {
   unsigned char* ptr = nullptr;   // device address of `scratch` on this GPU
+  int cus = 0, max_lds = 0;       // constants of the GPU
   size_t match_lds = 0;           // dynamic LDS the matching kernels are prepared for
   size_t dualptr_lds = 0;
   bool has_last = false;          // a call completed since the last failure
@@ -1155,19 +1156,6 @@ bool same_config(const avsg_config& a, const avsg_config& b) {
          a.match_mode == b.match_mode && a.gather_mode == b.gather_mode;
 }
 
-// n values produced by value(i), written to device memory through kernel
-// arguments (no host staging that must outlive the call)
-template <typename F>
-hipError_t put_values(unsigned long long* dst, size_t n, F value, hipStream_t s) {
-  unsigned long long chunk[120];
-  for (size_t i = 0; i < n; i += 120) {
-    const size_t m = std::min<size_t>(120, n - i);
-    for (size_t k = 0; k < m; ++k) chunk[k] = value(i + k);
-    const hipError_t e = launch_put_u64(dst + i, chunk, m, s);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
 }  // namespace
 
 extern "C" avsg_status avsg_step_static(const avsg_config* cfg, const void* const* host_rows,
@@ -1207,6 +1195,10 @@ extern "C" avsg_status avsg_step_static(const avsg_config* cfg, const void* cons
       std::fprintf(stderr, "avsg_step_static: hipGetSymbolAddress: %s\n", hipGetErrorString(e));
       return AVSG_E_HIP;
     }
+    int lds = 0;
+    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return AVSG_E_HIP;
+    sd.cus = device_cus();
+    sd.max_lds = lds;
     sd.ptr = static_cast<unsigned char*>(p);
   }
   if (!cold_start && !(sd.has_last && same_config(sd.last, c))) {
@@ -1220,12 +1212,10 @@ extern "C" avsg_status avsg_step_static(const avsg_config* cfg, const void* cons
   h.cfg = c;
   h.device = dev;
   h.m = log2_exact(c.slots);
-  h.cus = device_cus();
+  h.cus = sd.cus;
   bind_workspace(&h, sd.ptr, L, AVSG_STATIC_SCRATCH_BYTES, h.cus);
   h.workers = c.gather_workers > 0 ? c.gather_workers : std::max(1, h.cus);
-  int max_lds = 0;
-  if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-    return AVSG_E_HIP;
+  const int max_lds = sd.max_lds;
   if (c.match_mode == AVSG_MATCH_HASH) {
     h.lds = stage_one_lds_bytes(c.slots, c.topk, c.n_q, has_plan(c));
     if (h.ahead.served > 0) h.lds = std::max(h.lds, ahead_lds_bytes(c.slots, h.ahead.entries, h.ahead.quota));
@@ -1242,36 +1232,52 @@ extern "C" avsg_status avsg_step_static(const avsg_config* cfg, const void* cons
     }
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t B = static_cast<size_t>(c.batch), nsb = static_cast<size_t>(c.n_streams) * B;
-  for (size_t i = 0; i < nsb; ++i) {
+  const int B = c.batch, nsb = c.n_streams * B;
+  // every row array is looked at before anything is enqueued; the set-up
+  // launches take the addresses found here
+  static_assert(kMaxBatch * AVSG_MAX_STREAMS * sizeof(uint64_t) <= 16384, "addresses on the stack");
+  uint64_t rows_dev[kMaxBatch * AVSG_MAX_STREAMS];
+  for (int i = 0; i < nsb; ++i) {
     void* dp = nullptr;
     if (hipHostGetDevicePointer(&dp, const_cast<void*>(host_rows[i]), 0) != hipSuccess || !dp) {
       std::fprintf(stderr, "avsg_step_static: host rows must be pinned, device-mapped memory\n");
       return AVSG_E_INVAL;
     }
+    rows_dev[i] = reinterpret_cast<uint64_t>(dp);
   }
-  hipError_t e = put_values(
-      reinterpret_cast<unsigned long long*>(h.host_ptrs), nsb,
-      [&](size_t i) {
-        void* dp = nullptr;
-        (void)hipHostGetDevicePointer(&dp, const_cast<void*>(host_rows[i]), 0);
-        return static_cast<unsigned long long>(reinterpret_cast<uintptr_t>(dp));
-      },
-      s);
-  if (e == hipSuccess)
-    e = put_values(reinterpret_cast<unsigned long long*>(h.buf_ptrs), nsb,
-                   [&](size_t i) { return static_cast<unsigned long long>(reinterpret_cast<uintptr_t>(d_buffers[i])); },
-                   s);
-  if (e == hipSuccess)
-    e = put_values(reinterpret_cast<unsigned long long*>(h.rows_dev), B,
-                   [&](size_t i) { return static_cast<unsigned long long>(rows_per_request[i]); }, s);
-  if (e == hipSuccess && cold_start) {
-    // every table empty and the counters at zero (fill kernels)
-    if (c.match_mode == AVSG_MATCH_HASH)
-      e = launch_reset_tables(h.table_c, h.table_q, B * static_cast<size_t>(c.slots), s);
-    else
-      e = launch_reset_dualptr(h.dp_state, c.batch, c.topk, s);
-    if (e == hipSuccess) e = launch_zero_u64(h.stats, B * kNumStats, s);
+  StaticSetup a{};
+  a.host_ptrs = reinterpret_cast<unsigned long long*>(h.host_ptrs);
+  a.buf_ptrs = reinterpret_cast<unsigned long long*>(h.buf_ptrs);
+  a.rows = reinterpret_cast<unsigned long long*>(h.rows_dev);
+  a.ptrs = nsb;
+  a.pair_period = 1;
+  if (cold_start) {
+    // every table empty and the counters at zero
+    if (c.match_mode == AVSG_MATCH_HASH) {
+      a.table_c = h.table_c;
+      a.table_q = h.table_q;
+      a.table_words = static_cast<size_t>(B) * c.slots;
+    } else {
+      a.pair = h.dp_state;
+      a.pairs = static_cast<size_t>(B) * c.topk;
+      a.pair_period = c.topk;
+    }
+    a.stats = h.stats;
+    a.n_stats = static_cast<size_t>(B) * kNumStats;
+  }
+  hipError_t e = hipSuccess;
+  const int values = 2 * nsb + B;
+  for (int first = 0; first < values && e == hipSuccess; first += kSetupWords) {
+    a.first = first;
+    a.n = std::min(kSetupWords, values - first);
+    for (int i = 0; i < a.n; ++i) {
+      const int k = first + i;
+      a.v[i] = k < nsb       ? rows_dev[k]
+               : k < 2 * nsb ? reinterpret_cast<uint64_t>(d_buffers[k - nsb])
+                             : static_cast<uint64_t>(rows_per_request[k - 2 * nsb]);
+    }
+    e = launch_static_setup(a, s);
+    a.table_words = a.pairs = a.n_stats = 0;
   }
   if (e != hipSuccess) {
     std::fprintf(stderr, "avsg_step_static: %s\n", hipGetErrorString(e));

@@ -190,6 +190,26 @@ struct DualPtrParams {
   unsigned long long* stats;    // [B][kNumStats]
 };
 
+// Arguments of avsg_step_static's set-up kernel (4 KB of kernel arguments hold
+// the values of one launch; more of them go in further launches).
+constexpr int kSetupWords = 480;
+struct StaticSetup {
+  unsigned long long *host_ptrs, *buf_ptrs, *rows;
+  int32_t ptrs;                 // entries of host_ptrs and of buf_ptrs
+  int32_t first, n;             // values [first, first + n) of [host_ptrs | buf_ptrs | rows]
+  int32_t pair_period;
+  // cold start: hash tables or (index, slot) pairs to empty, counters to zero (0: none)
+  int32_t* table_c;
+  uint32_t* table_q;
+  size_t table_words;
+  int2* pair;
+  size_t pairs;
+  unsigned long long* stats;
+  size_t n_stats;
+  unsigned long long v[kSetupWords];
+};
+static_assert(sizeof(StaticSetup) <= 4096, "one launch's arguments");
+
 // LDS bytes of the matching kernel for (S, K); 0 if K exceeds the supported
 // indices per thread.
 size_t match_lds_bytes(int S, int K);
@@ -208,9 +228,7 @@ hipError_t launch_zero_u64(unsigned long long* p, size_t n, hipStream_t s);
 // repeated, 3 both, 0 valid); K <= 8192
 hipError_t launch_validate_topk(const int32_t* topk, const int64_t* rows, int B, int n_q, int K,
                                 int32_t* verdict, hipStream_t s);
-// n 64-bit values from host memory to device memory through kernel arguments
-// (the host array may be reused as soon as the call returns)
-hipError_t launch_put_u64(unsigned long long* dst, const unsigned long long* v, size_t n, hipStream_t s);
+hipError_t launch_static_setup(const StaticSetup& a, hipStream_t s);
 hipError_t launch_gather_balanced(const GatherParams& p, int workers, hipStream_t s);
 hipError_t launch_gather_request(const GatherParams& p, hipStream_t s);
 hipError_t launch_gather_position(const GatherParams& p, int workers, hipStream_t s);

@@ -34,6 +34,8 @@
 // into the write back.  With the resident-reuse gather the workgroup then
 // plans Stage Two (plan_request): which misses need the host link and which
 // can be filled from a slot that already holds their row.
+#include <algorithm>
+
 #include "fetch_body.h"
 #include "match_body.h"
 
@@ -114,19 +116,27 @@ __global__ __launch_bounds__(kValidateThreads) void validate_topk_kernel(const i
   if (tid == 0) verdict[row] = flags;
 }
 
-// Values written by one launch of put_u64_kernel; the chunk travels in the
-// kernel arguments, so a caller's host array needs to live only for the launch
-// call.
-constexpr int kPutWords = 120;
-struct PutChunk {
-  unsigned long long* dst;
-  int32_t n;
-  int32_t pad;
-  unsigned long long v[kPutWords];
-};
-
-__global__ void put_u64_kernel(PutChunk c) {
-  for (int i = static_cast<int>(threadIdx.x); i < c.n; i += static_cast<int>(blockDim.x)) c.dst[i] = c.v[i];
+// Everything avsg_step_static sets up before its step, in one launch: the
+// pointer tables and row counts, whose values travel in the kernel arguments
+// (a caller's host arrays need to live only for the launch call), and for a
+// cold start empty tables and zero counters.  As five kernels of 1.6 us each
+// with the gaps between them it took longer than the matching kernel behind it.
+__global__ __launch_bounds__(256) void static_setup_kernel(StaticSetup a) {
+  const size_t t = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
+  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
+  if (blockIdx.x == 0)
+    for (int i = static_cast<int>(threadIdx.x); i < a.n; i += static_cast<int>(blockDim.x)) {
+      const int k = a.first + i;   // place among [host_ptrs | buf_ptrs | rows]
+      unsigned long long* d = k < a.ptrs ? a.host_ptrs + k
+                              : k < 2 * a.ptrs ? a.buf_ptrs + (k - a.ptrs) : a.rows + (k - 2 * a.ptrs);
+      *d = a.v[i];
+    }
+  for (size_t j = t; j < a.table_words; j += stride) {
+    a.table_c[j] = -1;
+    a.table_q[j] = kEmptyWord;
+  }
+  for (size_t j = t; j < a.pairs; j += stride) a.pair[j] = make_int2(-1, static_cast<int>(j % a.pair_period));
+  for (size_t j = t; j < a.n_stats; j += stride) a.stats[j] = 0ull;
 }
 
 }  // namespace
@@ -147,17 +157,11 @@ hipError_t launch_validate_topk(const int32_t* topk, const int64_t* rows, int B,
   return hipGetLastError();
 }
 
-hipError_t launch_put_u64(unsigned long long* dst, const unsigned long long* v, size_t n, hipStream_t s) {
-  for (size_t i = 0; i < n; i += kPutWords) {
-    PutChunk c{};
-    c.dst = dst + i;
-    c.n = static_cast<int32_t>(n - i < static_cast<size_t>(kPutWords) ? n - i : kPutWords);
-    for (int k = 0; k < c.n; ++k) c.v[k] = v[i + k];
-    hipLaunchKernelGGL(put_u64_kernel, dim3(1), dim3(128), 0, s, c);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+hipError_t launch_static_setup(const StaticSetup& a, hipStream_t s) {
+  const size_t most = std::max(a.table_words, std::max(a.pairs, a.n_stats));
+  const size_t blocks = std::min<size_t>(std::max<size_t>((most + 1023) / 1024, 1), 1024);
+  hipLaunchKernelGGL(static_setup_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, a);
+  return hipGetLastError();
 }
 
 // Threads of the matching workgroup for (S, K): a table of at most 1024 slots
