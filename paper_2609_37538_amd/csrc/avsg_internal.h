@@ -190,9 +190,12 @@ struct DualPtrParams {
   unsigned long long* stats;    // [B][kNumStats]
 };
 
-// Arguments of avsg_step_static's set-up kernel (4 KB of kernel arguments hold
-// the values of one launch; more of them go in further launches).
-constexpr int kSetupWords = 480;
+// Arguments of avsg_step_static's set-up kernel.  4 KB of kernel arguments hold
+// at most 480 values, more of them go in further launches; a launch with few
+// takes the short form, since the runtime's argument memory is what bounds the
+// number of launches in flight (at 4 KB each, 400 calls in a row waited for it).
+constexpr int kSetupWords = 480, kSetupWordsShort = 48;
+template <int WORDS>
 struct StaticSetup {
   unsigned long long *host_ptrs, *buf_ptrs, *rows;
   int32_t ptrs;                 // entries of host_ptrs and of buf_ptrs
@@ -206,9 +209,9 @@ struct StaticSetup {
   size_t pairs;
   unsigned long long* stats;
   size_t n_stats;
-  unsigned long long v[kSetupWords];
+  unsigned long long v[WORDS];
 };
-static_assert(sizeof(StaticSetup) <= 4096, "one launch's arguments");
+static_assert(sizeof(StaticSetup<kSetupWords>) <= 4096, "one launch's arguments");
 
 // LDS bytes of the matching kernel for (S, K); 0 if K exceeds the supported
 // indices per thread.
@@ -228,7 +231,7 @@ hipError_t launch_zero_u64(unsigned long long* p, size_t n, hipStream_t s);
 // repeated, 3 both, 0 valid); K <= 8192
 hipError_t launch_validate_topk(const int32_t* topk, const int64_t* rows, int B, int n_q, int K,
                                 int32_t* verdict, hipStream_t s);
-hipError_t launch_static_setup(const StaticSetup& a, hipStream_t s);
+hipError_t launch_static_setup(const StaticSetup<kSetupWords>& a, hipStream_t s);
 hipError_t launch_gather_balanced(const GatherParams& p, int workers, hipStream_t s);
 hipError_t launch_gather_request(const GatherParams& p, hipStream_t s);
 hipError_t launch_gather_position(const GatherParams& p, int workers, hipStream_t s);

@@ -35,6 +35,8 @@
 // plans Stage Two (plan_request): which misses need the host link and which
 // can be filled from a slot that already holds their row.
 #include <algorithm>
+#include <cstddef>
+#include <cstring>
 
 #include "fetch_body.h"
 #include "match_body.h"
@@ -121,7 +123,8 @@ __global__ __launch_bounds__(kValidateThreads) void validate_topk_kernel(const i
 // (a caller's host arrays need to live only for the launch call), and for a
 // cold start empty tables and zero counters.  As five kernels of 1.6 us each
 // with the gaps between them it took longer than the matching kernel behind it.
-__global__ __launch_bounds__(256) void static_setup_kernel(StaticSetup a) {
+template <int WORDS>
+__global__ __launch_bounds__(256) void static_setup_kernel(StaticSetup<WORDS> a) {
   const size_t t = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
   const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
   if (blockIdx.x == 0)
@@ -157,10 +160,17 @@ hipError_t launch_validate_topk(const int32_t* topk, const int64_t* rows, int B,
   return hipGetLastError();
 }
 
-hipError_t launch_static_setup(const StaticSetup& a, hipStream_t s) {
+hipError_t launch_static_setup(const StaticSetup<kSetupWords>& a, hipStream_t s) {
   const size_t most = std::max(a.table_words, std::max(a.pairs, a.n_stats));
-  const size_t blocks = std::min<size_t>(std::max<size_t>((most + 1023) / 1024, 1), 1024);
-  hipLaunchKernelGGL(static_setup_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, a);
+  const dim3 blocks(static_cast<unsigned>(std::min<size_t>(std::max<size_t>((most + 1023) / 1024, 1), 1024)));
+  if (a.n <= kSetupWordsShort) {
+    StaticSetup<kSetupWordsShort> b;
+    static_assert(offsetof(StaticSetup<kSetupWordsShort>, v) == offsetof(StaticSetup<kSetupWords>, v), "same fields");
+    std::memcpy(static_cast<void*>(&b), &a, sizeof(b));
+    hipLaunchKernelGGL(static_setup_kernel<kSetupWordsShort>, blocks, dim3(256), 0, s, b);
+  } else {
+    hipLaunchKernelGGL(static_setup_kernel<kSetupWords>, blocks, dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -9,8 +9,8 @@ from test_zz_no_alloc import _run_pair
 pytestmark = pytest.mark.gpu
 
 
-# two streams: 5 values per request, 480 per launch
-@pytest.mark.parametrize("batch", [96, 97, 300])
+# two streams: 5 values per request, 480 per launch, up to 48 in the short form
+@pytest.mark.parametrize("batch", [9, 10, 96, 97, 300])
 @pytest.mark.parametrize("gather_mode", [0, 6], ids=["balanced", "resident"])
 def test_static_setup_many_requests(batch, gather_mode):
     spec = W.custom_spec(name=f"static_setup_{batch}", batch=batch, topk=16, slots=64, n_q=2, steps=4, ctx=200,
