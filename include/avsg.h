@@ -190,8 +190,10 @@ avsg_status avsg_resolve_config(const avsg_config *cfg, avsg_config *out);
  * with hash matching, up to 224 requests and at least 512 indices per request
  * and step, at most 2.5 MB of staging rows and tables
  * for the host rows that AVSG_GATHER_RESIDENT and AVSG_GATHER_BALANCED read
- * while Stage One runs: avsg_create also takes a workspace without that part
- * and then reads every host row after Stage One).  Returns 0 for an invalid
+ * while Stage One runs, and with AVSG_GATHER_RESIDENT and four tokens per step
+ * 4*N_q*K bytes per request and the plan's map words once more: avsg_create
+ * also takes a workspace without these parts, and then reads every host row
+ * after Stage One and copies the last repeats in a launch of their own).  Returns 0 for an invalid
  * cfg. */
 size_t avsg_workspace_bytes(const avsg_config *cfg);
 
@@ -331,8 +333,9 @@ avsg_status avsg_export_early(avsg_handle *h, int32_t r, int32_t *n_out, int32_t
  * avsg_timing copies up to `cap` recorded steps (synchronizing):
  * match_ms[i] is the duration of step i's matching kernel, gather_ms[i] that
  * of its main Stage Two kernel (or copies), and tail_ms[i] (may be NULL) the
- * rest of Stage Two: the repeat copies of AVSG_GATHER_RESIDENT with four or
- * more tokens per step, 0 otherwise.  AVSG_GATHER_EARLY: match_ms is the early
+ * rest of Stage Two: the repeat copies of AVSG_GATHER_RESIDENT with more than
+ * four tokens per step (four in a workspace without its optional parts), 0
+ * otherwise.  AVSG_GATHER_EARLY: match_ms is the early
  * list kernel, gather_ms the launch that matches and copies, tail_ms the
  * finishing kernel. */
 avsg_status avsg_set_timing(avsg_handle *h, int32_t enable);

@@ -34,6 +34,8 @@ struct avsg_handle {
   uint8_t* hit_mask = nullptr;
   int2* host_list = nullptr;    // resident-reuse plan (AVSG_GATHER_RESIDENT)
   int2* host_fan = nullptr;
+  int32_t* host_third = nullptr;   // four tokens per step: a third slot per host entry, and by map position
+  int32_t* plan_third = nullptr;
   int2* res_list = nullptr;
   int2* rep_list = nullptr;
   int32_t* plan_counts = nullptr;  // [B][3]
@@ -100,6 +102,12 @@ constexpr int kMaxBatch = 1024;
 constexpr size_t kMaxTimedSteps = 16384;
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;   // gfx950
 constexpr int kRepeatWorkersPerCu = 4;
+// Tokens per step at which a host entry has a third further slot: an index is
+// then missed at most four times in a step, so the host copy of its row and
+// its fan slots leave one repeat at most.  Without it a further launch copied
+// those few rows (one request 38.1 us per step with it, 34.9 without; 32
+// requests 353.0 and 348.4, 8 requests with K = 512 45.1 and 40.7).
+constexpr int kThirdTokens = 4;
 constexpr int kEarlyStagingRows = 16384;   // default staging capacity of the early-fetch transfer
 constexpr int kEarlyWorkers = 32;          // default copy workgroups beside the matching ones
 constexpr int kAheadWorkgroups = 32;       // look-ahead fetch: workgroups beside the matching ones
@@ -147,7 +155,9 @@ size_t pipe_chunks_for(const avsg_config& c);
 struct Layout {
   size_t table_c, table_q, miss_list, hit_mask, plan, early, pipe, pipe_bytes, stats, host_ptrs, buf_ptrs,
       rows, val, total;
-  size_t ahead_table, ahead_rows0, ahead_rows1, with_ahead;   // past `total`: used when the workspace holds it
+  // past `total`: each used when the workspace holds it
+  size_t ahead_table, ahead_rows0, ahead_rows1, with_ahead;
+  size_t host_third, plan_third, with_third;
 };
 
 bool has_plan(const avsg_config& c) {
@@ -235,6 +245,13 @@ Layout layout_of(const avsg_config& c) {
   L.ahead_rows1 = off;
   if (c.n_streams > 1) off += up(wgs * a.quota * static_cast<size_t>(c.row_bytes[1]));
   L.with_ahead = off;
+  // resident reuse with four tokens per step: a third further slot per host entry
+  L.host_third = off;
+  const bool third = c.gather_mode == AVSG_GATHER_RESIDENT && c.n_q == kThirdTokens;
+  if (third) off += up(B * static_cast<size_t>(c.n_q) * c.topk * 4);
+  L.plan_third = off;
+  if (third) off += up(B * static_cast<size_t>(plan_map_words(c.slots, c.topk, c.n_q)) * 4);
+  L.with_third = off;
   return L;
 }
 
@@ -404,6 +421,11 @@ void bind_workspace(avsg_handle* h, unsigned char* ws, const Layout& L, size_t b
     h->ahead.stage0 = reinterpret_cast<uint64_t>(ws + L.ahead_rows0);
     h->ahead.stage1 = c.n_streams > 1 ? reinterpret_cast<uint64_t>(ws + L.ahead_rows1) : 0;
   }
+  h->host_third = h->plan_third = nullptr;
+  if (L.with_third > L.host_third && bytes >= L.with_third) {
+    h->host_third = reinterpret_cast<int32_t*>(ws + L.host_third);
+    h->plan_third = reinterpret_cast<int32_t*>(ws + L.plan_third);
+  }
 }
 
 // Request sizes, and host-row and buffer addresses aligned for the copies.
@@ -441,7 +463,7 @@ avsg_status avsg_check_config(const avsg_config* cfg) { return check_config(cfg,
 
 size_t avsg_workspace_bytes(const avsg_config* cfg) {
   if (check_config(cfg, nullptr) != AVSG_OK) return 0;
-  return layout_of(resolved(*cfg)).with_ahead;
+  return layout_of(resolved(*cfg)).with_third;
 }
 
 avsg_status avsg_resolve_config(const avsg_config* cfg, avsg_config* out) {
@@ -761,6 +783,8 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
       p.plan_scan_off = h->plan_scan_off;
       p.host_list = h->host_list;
       p.host_fan = h->host_fan;
+      p.host_third = h->host_third;
+      p.plan_third = h->plan_third;
       p.res_list = h->res_list;
       p.rep_list = h->rep_list;
       p.plan_counts = h->plan_counts;
@@ -789,6 +813,9 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
   g.row_bytes1 = c.n_streams > 1 ? c.row_bytes[1] : 0;
   g.topk = d_topk; g.slots = d_slots; g.hit_mask = h->hit_mask;
   g.ahead = h->ahead;
+  // a fourth event only when Stage Two has a tail kernel (each record costs
+  // the step stream a few microseconds)
+  const bool tail = c.gather_mode == AVSG_GATHER_RESIDENT && c.n_q > 3 && !h->plan_third;
   switch (c.gather_mode) {
     case AVSG_GATHER_BALANCED: HIP_TRY(h, launch_gather_balanced(g, h->workers, s)); break;
     case AVSG_GATHER_REQUEST: HIP_TRY(h, launch_gather_request(g, s)); break;
@@ -798,15 +825,15 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
       // kernel, then the repeats left over
       GatherParams gh = g, gr = g;
       gh.miss_counts = h->plan_counts; gh.counts_per_req = 1; gh.count_stride = 3;
-      gh.miss_list = h->host_list; gh.fan = h->host_fan;
+      gh.miss_list = h->host_list; gh.fan = h->host_fan; gh.third = h->host_third;
       gr.miss_counts = h->plan_counts + 1; gr.counts_per_req = 1; gr.count_stride = 3;
       gr.miss_list = h->res_list;
       HIP_TRY(h, launch_gather_resident(gh, gr, h->plan_claim, h->workers, s));
       if ((rc = record(h, 2, s)) != AVSG_OK) return rc;
-      // the host copies also fill each index's two largest repeats, so
-      // repeats are left only with four or more tokens per step; they are few
-      // and HBM-latency bound, so they get more, smaller workgroups
-      if (c.n_q > 3) {
+      // the host copies also fill each index's two largest repeats (three with
+      // four tokens), so repeats are left only with more tokens per step; they
+      // are few and HBM-latency bound, so they get more, smaller workgroups
+      if (tail) {
         g.miss_counts = h->plan_counts + 2; g.counts_per_req = 1; g.count_stride = 3;
         g.miss_list = h->rep_list;
         HIP_TRY(h, launch_copy_device(g, kRepeatWorkersPerCu * std::max(1, h->cus), s));
@@ -818,9 +845,6 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
       break;
     default: break;
   }
-  // a fourth event only when Stage Two has a tail kernel (each record costs
-  // the step stream a few microseconds)
-  const bool tail = c.gather_mode == AVSG_GATHER_RESIDENT && c.n_q > 3;
   if (c.gather_mode != AVSG_GATHER_RESIDENT && (rc = record(h, 2, s)) != AVSG_OK) return rc;
   if (tail && (rc = record(h, 3, s)) != AVSG_OK) return rc;
   if (h->timing && h->n_timed < kMaxTimedSteps) h->has_tail[h->n_timed++] = tail;

@@ -88,6 +88,8 @@ struct MatchParams {
   int32_t plan_scan_off;        // LDS byte offset of the scan's per-wave candidate lists (0: none)
   int2* host_list;              // [B][n_q*K] (index, slot) copied from the host
   int2* host_fan;               // [B][n_q*K] the two further slots a host entry is also copied to (-1: none)
+  int32_t* host_third;          // [B][n_q*K] a third further slot (-1: none), with plan_third
+  int32_t* plan_third;          // [B][plan_words] that slot by map position (four tokens per step), or nullptr
   int2* res_list;               // [B][n_q*K] (source slot, slot): row already resident
   int2* rep_list;               // [B][n_q*K] (source slot, slot): repeat of a host entry
   int32_t* plan_counts;         // [B][3] host, resident, repeat entries
@@ -124,6 +126,7 @@ struct GatherParams {
   int32_t counts_per_req, count_stride;
   const int2* miss_list;        // [B][n_q*K] (index or source slot, slot)
   const int2* fan;              // [B][n_q*K] two further destination slots per entry (-1: none), or nullptr
+  const int32_t* third;         // [B][n_q*K] a third further slot per entry (-1: none), or nullptr
   const int64_t* rows;          // [B]
   int32_t n_streams;
   const uint64_t* host_ptrs;    // [n_streams][B] device-visible addresses of host row 0

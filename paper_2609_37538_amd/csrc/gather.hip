@@ -14,7 +14,7 @@
 // into C near-equal contiguous ranges; hit positions issue no copy but still
 // occupy their worker's share.  With the resident-reuse plan of the matching
 // kernel, the resident kernel copies the host list (each row also to its two
-// fan slots) and the rows already in the device buffer; with four or more
+// fan slots) and the rows already in the device buffer; with more than four
 // tokens per step the device-copy kernel then fills the repeats left over.
 #include "gather_body.h"
 
@@ -95,7 +95,8 @@ template <bool kDevice>
 __device__ void copy_tiles(const GatherParams& p, const int* pre, int n, int T, int first, int base, int* counter,
                            int* next, uint64_t* src0, uint64_t* dst0, uint64_t* src1, uint64_t* dst1,
                            uint64_t* dstx0 = nullptr, uint64_t* dstx1 = nullptr, uint64_t* dsty0 = nullptr,
-                           uint64_t* dsty1 = nullptr, const int* cov = nullptr) {
+                           uint64_t* dsty1 = nullptr, const int* cov = nullptr, uint64_t* dstz0 = nullptr,
+                           uint64_t* dstz1 = nullptr) {
   int t0 = first;
   for (;;) {
     if (t0 < 0) {
@@ -107,17 +108,22 @@ __device__ void copy_tiles(const GatherParams& p, const int* pre, int n, int T, 
     }
     if (t0 >= n) break;
     copy_range<kDevice>(p, pre, t0, t0 + T < n ? t0 + T : n, src0, dst0, src1, dst1, dstx0, dstx1, dsty0,
-                        dsty1, cov);
+                        dsty1, cov, -1, dstz0, dstz1);
     t0 = -1;
   }
 }
 
+// THIRD: host entries have a third further slot (four tokens per step).
+template <bool THIRD>
 __global__ __launch_bounds__(GT) void gather_resident_kernel(GatherParams hp, GatherParams rp,
                                                               int* claim) {
   __shared__ int pre_h[kMaxBatch + 1], pre_r[kMaxBatch + 1], cov[kMaxBatch];
   __shared__ int wtot[2 * (GT / 64)];
   __shared__ uint64_t src0[TILE], dst0[TILE], src1[TILE], dst1[TILE], dstx0[TILE], dstx1[TILE], dsty0[TILE],
       dsty1[TILE];
+  __shared__ uint64_t dstz[THIRD ? 2 * TILE : 1];
+  uint64_t* const dstz0 = THIRD ? dstz : nullptr;
+  uint64_t* const dstz1 = THIRD ? dstz + TILE : nullptr;
   __shared__ int next;
   const int C = static_cast<int>(gridDim.x), w = static_cast<int>(blockIdx.x);
   const int B = hp.B;
@@ -138,7 +144,8 @@ __global__ __launch_bounds__(GT) void gather_resident_kernel(GatherParams hp, Ga
     const int lo = k * T;
     const int hi = lo + T < cnt ? lo + T : cnt;
     if (lo < hi)
-      copy_range<false>(hp, nullptr, lo, hi, src0, dst0, src1, dst1, dstx0, dstx1, dsty0, dsty1, nullptr, r);
+      copy_range<false>(hp, nullptr, lo, hi, src0, dst0, src1, dst1, dstx0, dstx1, dsty0, dsty1, nullptr, r,
+                        dstz0, dstz1);
   }
   // the rest of the host list, batch-wide (every group; without first tiles
   // tile w goes first to host-first workgroup w), then claimed tiles, and the
@@ -154,10 +161,10 @@ __global__ __launch_bounds__(GT) void gather_resident_kernel(GatherParams hp, Ga
     const int i = C - 1 - w;       // 0 .. cr-1
     copy_tiles<true>(rp, pre_r, R, tr, i * tr, res_base, claim, &next, src0, dst0, src1, dst1);
     copy_tiles<false>(hp, pre_h, N, kHostTile, -1, host_base, claim + 1, &next, src0, dst0, src1, dst1,
-                      dstx0, dstx1, dsty0, dsty1, cov);
+                      dstx0, dstx1, dsty0, dsty1, cov, dstz0, dstz1);
   } else {
     copy_tiles<false>(hp, pre_h, N, th, first_on ? -1 : w * th, host_base, claim + 1, &next, src0, dst0, src1, dst1,
-                      dstx0, dstx1, dsty0, dsty1, cov);
+                      dstx0, dstx1, dsty0, dsty1, cov, dstz0, dstz1);
     copy_tiles<true>(rp, pre_r, R, tr, -1, res_base, claim, &next, src0, dst0, src1, dst1);
   }
 }
@@ -227,7 +234,10 @@ hipError_t launch_copy_device(const GatherParams& p, int workers, hipStream_t s)
 hipError_t launch_gather_resident(const GatherParams& host, const GatherParams& dev, int* claim,
                                   int workers, hipStream_t s) {
   if (workers < 1 || host.B > kMaxBatch || !claim || !host.fan) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gather_resident_kernel, dim3(workers), dim3(GT), 0, s, host, dev, claim);
+  if (host.third)
+    hipLaunchKernelGGL(gather_resident_kernel<true>, dim3(workers), dim3(GT), 0, s, host, dev, claim);
+  else
+    hipLaunchKernelGGL(gather_resident_kernel<false>, dim3(workers), dim3(GT), 0, s, host, dev, claim);
   return hipGetLastError();
 }
 

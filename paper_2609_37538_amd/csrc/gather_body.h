@@ -155,16 +155,16 @@ __device__ __forceinline__ int find_request(const T* pre, int B, T j) {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Rows i < tn: copy chunks * sizeof(V) bytes from src[i] to dst[i] (src[i] == 0
-// skips the row), and also to dstx[i] and dsty[i] where those are given and
-// nonzero, with NT threads each keeping U loads in flight.
+// skips the row), and also to dstx[i], dsty[i] and dstz[i] where those are
+// given and nonzero, with NT threads each keeping U loads in flight.
 template <typename V, int U = kUnroll, int NT = GT>
 __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* dst, int tn,
                                           int chunks, const uint64_t* dstx = nullptr,
-                                          const uint64_t* dsty = nullptr) {
+                                          const uint64_t* dsty = nullptr, const uint64_t* dstz = nullptr) {
   const int total = tn * chunks;
   for (int q0 = threadIdx.x; q0 < total; q0 += NT * U) {
     V v[U];
-    uint64_t sa[U], da[U], xa[U], ya[U];
+    uint64_t sa[U], da[U], xa[U], ya[U], za[U];
     // addresses first, then every load, then the stores: nothing stands
     // between the loads, so a thread's U loads are in flight together
 #pragma unroll
@@ -178,6 +178,7 @@ __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* d
       da[u] = dst[i] + off;
       xa[u] = dstx && dstx[i] ? dstx[i] + off : 0;
       ya[u] = dsty && dsty[i] ? dsty[i] + off : 0;
+      za[u] = dstz && dstz[i] ? dstz[i] + off : 0;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -188,6 +189,7 @@ __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* d
         store_global<V>(da[u], v[u]);
         if (xa[u]) store_global<V>(xa[u], v[u]);
         if (ya[u]) store_global<V>(ya[u], v[u]);
+        if (za[u]) store_global<V>(za[u], v[u]);
       }
   }
 }
@@ -211,7 +213,7 @@ __device__ inline void copy_tile_rows(const GatherParams& p, int tn, uint64_t* s
 // Copy entries [a, b) of the batch-wide list.  kDevice: an entry is (source
 // slot, slot) of the request's own buffers; otherwise (host row, slot), and
 // with p.fan and staging for it (dstx0/1, dsty0/1), the row also goes to the
-// entry's fan slots.  Entry j of the batch-wide list is entry cov[r] + j -
+// entry's fan slots, and with p.third (dstz0/1) to a third one.  Entry j of the batch-wide list is entry cov[r] + j -
 // pre[r] of request r's list (cov: rows of each request left out of the
 // batch-wide list, or none); with fixed_r >= 0, [a, b) are entries of request
 // fixed_r's own list and pre is not read.
@@ -220,7 +222,8 @@ __device__ __forceinline__ void copy_range(const GatherParams& p, const int* pre
                            uint64_t* src0, uint64_t* dst0, uint64_t* src1, uint64_t* dst1,
                            uint64_t* dstx0 = nullptr, uint64_t* dstx1 = nullptr,
                            uint64_t* dsty0 = nullptr, uint64_t* dsty1 = nullptr,
-                           const int* cov = nullptr, int fixed_r = -1) {
+                           const int* cov = nullptr, int fixed_r = -1, uint64_t* dstz0 = nullptr,
+                           uint64_t* dstz1 = nullptr) {
   const size_t per_req = static_cast<size_t>(p.n_q) * p.K;
   for (int t0 = a; t0 < b; t0 += TILE) {
     const int tn = (b - t0) < TILE ? (b - t0) : TILE;
@@ -236,6 +239,8 @@ __device__ __forceinline__ void copy_range(const GatherParams& p, const int* pre
       const int2 e = p.miss_list[at];
       int2 fan = make_int2(-1, -1);
       if (dstx0) fan = p.fan[at];
+      int third = -1;
+      if (dstz0) third = p.third[at];
       const bool two = p.n_streams > 1;
       const int64_t rows_r = p.rows[r];
       const uint64_t buf0 = p.buf_ptrs[r], buf1 = two ? p.buf_ptrs[p.B + r] : 0;
@@ -260,10 +265,12 @@ __device__ __forceinline__ void copy_range(const GatherParams& p, const int* pre
       dst0[i] = buf0 + static_cast<uint64_t>(e.y) * p.row_bytes0;
       if (fan.x >= p.S) fan.x = -1;
       if (fan.y >= p.S) fan.y = -1;
+      if (third >= p.S) third = -1;
       if (dstx0) {
         dstx0[i] = fan.x >= 0 ? buf0 + static_cast<uint64_t>(fan.x) * p.row_bytes0 : 0;
         dsty0[i] = fan.y >= 0 ? buf0 + static_cast<uint64_t>(fan.y) * p.row_bytes0 : 0;
       }
+      if (dstz0) dstz0[i] = third >= 0 ? buf0 + static_cast<uint64_t>(third) * p.row_bytes0 : 0;
       if (two) {
         src1[i] = ok ? from1 + row * p.row_bytes1 : 0;
         dst1[i] = buf1 + static_cast<uint64_t>(e.y) * p.row_bytes1;
@@ -271,19 +278,20 @@ __device__ __forceinline__ void copy_range(const GatherParams& p, const int* pre
           dstx1[i] = fan.x >= 0 ? buf1 + static_cast<uint64_t>(fan.x) * p.row_bytes1 : 0;
           dsty1[i] = fan.y >= 0 ? buf1 + static_cast<uint64_t>(fan.y) * p.row_bytes1 : 0;
         }
+        if (dstz1) dstz1[i] = third >= 0 ? buf1 + static_cast<uint64_t>(third) * p.row_bytes1 : 0;
       }
     }
     __syncthreads();
     if ((p.row_bytes0 & 15) == 0)
-      copy_rows<u32x4, kDevice ? kUnroll : kHostUnroll>(src0, dst0, tn, static_cast<int>(p.row_bytes0 / 16), dstx0, dsty0);
+      copy_rows<u32x4, kDevice ? kUnroll : kHostUnroll>(src0, dst0, tn, static_cast<int>(p.row_bytes0 / 16), dstx0, dsty0, dstz0);
     else
-      copy_rows<uint32_t>(src0, dst0, tn, static_cast<int>(p.row_bytes0 / 4), dstx0, dsty0);
+      copy_rows<uint32_t>(src0, dst0, tn, static_cast<int>(p.row_bytes0 / 4), dstx0, dsty0, dstz0);
     if (p.n_streams > 1) {
       if ((p.row_bytes1 & 15) == 0)
         copy_rows<u32x4, kDevice ? kUnroll : kHostUnroll>(src1, dst1, tn, static_cast<int>(p.row_bytes1 / 16), dstx1,
-                                                          dsty1);
+                                                          dsty1, dstz1);
       else
-        copy_rows<uint32_t>(src1, dst1, tn, static_cast<int>(p.row_bytes1 / 4), dstx1, dsty1);
+        copy_rows<uint32_t>(src1, dst1, tn, static_cast<int>(p.row_bytes1 / 4), dstx1, dsty1, dstz1);
     }
     __syncthreads();
   }

@@ -222,24 +222,34 @@ struct PlanHash {
   __device__ __forceinline__ uint32_t next(uint32_t h) const { return h + 1u == P ? 0u : h + 1u; }
 };
 
-// A fan word: the two largest bids (slot + 1, nonzero, below 2^16), the larger
-// in the low 16 bits, 0 = no bid.  Bids of one word are distinct slots.
-__device__ __forceinline__ void fan_bid(uint32_t* w, uint32_t v) {
+// A fan word: the two largest bids (slot + 1, nonzero, below 2^15), the larger
+// in the low 16 bits, 0 = no bid; the top bit says that a further bid is in
+// neither.  Bids of one word are distinct slots.
+constexpr uint32_t kFanSlot = 0x7FFFu;
+constexpr uint32_t kFanMore = 0x80000000u;
+// Bids v; returns the bid that is now in neither field (0 = none): v itself or
+// the one it displaced.  With N_q <= 4 a word gets at most three bids, so at
+// most one call of its bids returns nonzero.
+__device__ __forceinline__ uint32_t fan_bid(uint32_t* w, uint32_t v) {
   uint32_t cur = *w;
   for (;;) {
-    const uint32_t a = cur & 0xFFFFu, b = cur >> 16;
-    uint32_t nw;
-    if (v > a) nw = v | (a << 16);
-    else if (v > b) nw = a | (v << 16);
-    else return;   // not among the two largest
+    const uint32_t a = cur & kFanSlot, b = (cur >> 16) & kFanSlot;
+    const uint32_t more = (cur & kFanMore) | (b != 0u ? kFanMore : 0u);
+    uint32_t nw, out = b;
+    if (v > a) nw = v | (a << 16) | more;
+    else if (v > b) nw = a | (v << 16) | more;
+    else {   // not among the two largest
+      nw = cur | kFanMore;
+      out = v;
+    }
     const uint32_t prev = atomicCAS(w, cur, nw);
-    if (prev == cur) return;
+    if (prev == cur) return out;
     cur = prev;
   }
 }
 // The two fan slots of a fan word (-1 = none).
 __device__ __forceinline__ int2 fan_slots(uint32_t w) {
-  return make_int2(static_cast<int>(w & 0xFFFFu) - 1, static_cast<int>(w >> 16) - 1);
+  return make_int2(static_cast<int>(w & kFanSlot) - 1, static_cast<int>((w >> 16) & kFanSlot) - 1);
 }
 
 // Position of index x's word in the map (its word in *word), or -1.
@@ -272,7 +282,9 @@ __device__ __forceinline__ int plan_lookup(const uint32_t* smp, const int32_t* s
 // A host entry also writes its row to the two largest repeat destinations of
 // its index (its fan slots: the second and third largest slots reserved for
 // the index), so with up to three tokens per step no repeat is left for a
-// later copy.  The lists keep transfer-list order.  LDS: a map of P words,
+// later copy; with four tokens the one repeat that can be left is kept beside
+// the fan slots in device memory (host_third) for the same copy, and listed as
+// a repeat all the same.  The lists keep transfer-list order.  LDS: a map of P words,
 // open addressing with linear probing keyed by the index a word names through
 // c[]; a word is (resident bit | early bit | tag | slot + 1), 0 = free, and
 // atomicMax makes every choice deterministic; beside it P fan words, one per
@@ -308,6 +320,9 @@ __device__ __forceinline__ void plan_request(const MatchParams& p, const int r, 
   const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
   const size_t lb = static_cast<size_t>(r) * p.n_q * p.K;
   const int2* ml = p.miss_list + lb;
+  // the repeat destination past the fan word's two, by map position (written
+  // where the word's top bit is set)
+  int32_t* third = p.plan_third + static_cast<size_t>(r) * P;
   // entry e of the transfer list: (index, slot)
   auto entry = [&](int e) __attribute__((always_inline)) {
     if (p.plan_list_off == 0) return ml[e];
@@ -341,7 +356,8 @@ __device__ __forceinline__ void plan_request(const MatchParams& p, const int r, 
         // two largest bids
         const uint32_t old = atomicMax(&smp[h], val | kPlanDisp);
         const int other = (old & kPlanSlot) < (val & kPlanSlot) ? plan_slot(old) : o;
-        fan_bid(&sfan[h], static_cast<uint32_t>(other) + 1u);
+        const uint32_t out = fan_bid(&sfan[h], static_cast<uint32_t>(other) + 1u);
+        if (out != 0u && p.plan_third) third[h] = static_cast<int32_t>(out) - 1;
         break;
       }
       if (t == 0) atomicOr(&smp[h], kPlanDisp);   // another index holds the home word
@@ -484,7 +500,12 @@ __device__ __forceinline__ void plan_request(const MatchParams& p, const int r, 
   for (int e0 = 0, it = 0; e0 < listed; e0 += MT, ++it) {
     Entry c = it == 0 ? first : classify(e0 + tid);
     int2 fan = make_int2(-1, -1);
-    if (c.kind == 0 && c.hw >= 0) fan = fan_slots(sfan[c.hw]);
+    int further = -1;
+    if (c.kind == 0 && c.hw >= 0) {
+      const uint32_t fw = sfan[c.hw];
+      fan = fan_slots(fw);
+      if (p.plan_third && (fw & kFanMore)) further = third[c.hw];
+    }
     if (c.kind == 2) {
       ++n_rep;
       const int2 f = fan_slots(sfan[c.hw]);
@@ -509,6 +530,7 @@ __device__ __forceinline__ void plan_request(const MatchParams& p, const int r, 
       const size_t at = lb + n_list[0] + before[0] + bits_below(mk[0]);
       p.host_list[at] = c.v;
       p.host_fan[at] = fan;
+      if (p.plan_third) p.host_third[at] = further;
     } else if (kind == 1) {
       p.res_list[lb + n_list[1] + before[1] + bits_below(mk[1])] = make_int2(c.src, c.v.y);
     } else if (kind == 2) {
