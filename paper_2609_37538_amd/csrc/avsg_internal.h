@@ -15,6 +15,16 @@ constexpr int kGatherTile = 64;
 // XCDs of an MI355X (gfx950): 8 accelerator dies of 32 CUs, each with its own L2.
 constexpr int kXcds = 8;
 
+// Sixteen bytes of a row at any 4-byte boundary (global memory takes a 16-byte
+// access of a lane there): a row of at least 16 bytes is ceil(bytes / 16) of
+// them, the last one over the row's last 16 bytes, so rows off the 16-byte grid
+// need no 4-byte accesses (132-byte rows 9 in place of 33, 580-byte rows 37 in
+// place of 145).
+// (The attribute belongs to the type's name and is lost in a template argument,
+// so functions name the type themselves.)
+typedef unsigned int chunk16 __attribute__((ext_vector_type(4)));
+typedef unsigned int row16 __attribute__((ext_vector_type(4), aligned(4)));
+
 // Loads and stores at a device-visible address held as a number, as global
 // memory accesses: through a plain pointer they become flat ones, which also
 // count as LDS accesses, so that a wave waits for its row loads in flight
@@ -26,6 +36,23 @@ __device__ __forceinline__ V load_global(uint64_t a) {
 template <typename V>
 __device__ __forceinline__ void store_global(uint64_t a, V v) {
   *reinterpret_cast<__attribute__((address_space(1))) V*>(a) = v;
+}
+__device__ __forceinline__ chunk16 load_row16(uint64_t a) {
+  return *reinterpret_cast<const __attribute__((address_space(1))) row16*>(a);
+}
+__device__ __forceinline__ void store_row16(uint64_t a, chunk16 v) {
+  *reinterpret_cast<__attribute__((address_space(1))) row16*>(a) = v;
+}
+// A chunk V of a row; kOffGrid: row16.
+template <typename V, bool kOffGrid>
+__device__ __forceinline__ V load_chunk(uint64_t a) {
+  if constexpr (kOffGrid) return load_row16(a);
+  else return load_global<V>(a);
+}
+template <typename V, bool kOffGrid>
+__device__ __forceinline__ void store_chunk(uint64_t a, V v) {
+  if constexpr (kOffGrid) store_row16(a, v);
+  else store_global<V>(a, v);
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave, register to register

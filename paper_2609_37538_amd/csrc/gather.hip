@@ -8,8 +8,8 @@
 // kernel (S1, Eq. 13) runs one workgroup per request.  Inside a workgroup a
 // tile of misses is staged in LDS as (source, destination) address pairs, and
 // the lanes copy the rows with 16-byte loads from pinned, device-mapped host
-// memory (4-byte loads for rows that are not a multiple of 16 bytes, such as
-// the 132-byte indexer-key rows), several loads in flight per lane.  The
+// memory (row16, at 4-byte boundaries for rows such as the 132-byte indexer-key
+// ones).  The
 // position kernel (S2, Eq. 14) splits the flattened N_g*K selected positions
 // into C near-equal contiguous ranges; hit positions issue no copy but still
 // occupy their worker's share.  With the resident-reuse plan of the matching
@@ -91,7 +91,7 @@ __device__ __forceinline__ int tile_rows(int n, int group, int max_rows) {
 // Copy tiles of T entries of a list of n entries: `first` (or none, -1) then
 // claimed tiles, which start at row `base` (none are left to claim, and no
 // claim is made, when that is the list's end).
-template <bool kDevice>
+template <bool kDevice, bool kRow16>
 __device__ void copy_tiles(const GatherParams& p, const int* pre, int n, int T, int first, int base, int* counter,
                            int* next, uint64_t* src0, uint64_t* dst0, uint64_t* src1, uint64_t* dst1,
                            uint64_t* dstx0 = nullptr, uint64_t* dstx1 = nullptr, uint64_t* dsty0 = nullptr,
@@ -107,7 +107,7 @@ __device__ void copy_tiles(const GatherParams& p, const int* pre, int n, int T, 
       __syncthreads();
     }
     if (t0 >= n) break;
-    copy_range<kDevice>(p, pre, t0, t0 + T < n ? t0 + T : n, src0, dst0, src1, dst1, dstx0, dstx1, dsty0,
+    copy_range<kDevice, kDevice ? kUnroll : kHostUnroll, kRow16>(p, pre, t0, t0 + T < n ? t0 + T : n, src0, dst0, src1, dst1, dstx0, dstx1, dsty0,
                         dsty1, cov, -1, dstz0, dstz1);
     t0 = -1;
   }
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(GT) void gather_resident_kernel(GatherParams hp, Ga
     const int lo = k * T;
     const int hi = lo + T < cnt ? lo + T : cnt;
     if (lo < hi)
-      copy_range<false>(hp, nullptr, lo, hi, src0, dst0, src1, dst1, dstx0, dstx1, dsty0, dsty1, nullptr, r,
+      copy_range<false, kHostUnroll, !THIRD>(hp, nullptr, lo, hi, src0, dst0, src1, dst1, dstx0, dstx1, dsty0, dsty1, nullptr, r,
                         dstz0, dstz1);
   }
   // the rest of the host list, batch-wide (every group; without first tiles
@@ -159,13 +159,13 @@ __global__ __launch_bounds__(GT) void gather_resident_kernel(GatherParams hp, Ga
   const int host_base = first_on ? 0 : ch * th;
   if (w >= ch) {
     const int i = C - 1 - w;       // 0 .. cr-1
-    copy_tiles<true>(rp, pre_r, R, tr, i * tr, res_base, claim, &next, src0, dst0, src1, dst1);
-    copy_tiles<false>(hp, pre_h, N, kHostTile, -1, host_base, claim + 1, &next, src0, dst0, src1, dst1,
+    copy_tiles<true, !THIRD>(rp, pre_r, R, tr, i * tr, res_base, claim, &next, src0, dst0, src1, dst1);
+    copy_tiles<false, !THIRD>(hp, pre_h, N, kHostTile, -1, host_base, claim + 1, &next, src0, dst0, src1, dst1,
                       dstx0, dstx1, dsty0, dsty1, cov, dstz0, dstz1);
   } else {
-    copy_tiles<false>(hp, pre_h, N, th, first_on ? -1 : w * th, host_base, claim + 1, &next, src0, dst0, src1, dst1,
+    copy_tiles<false, !THIRD>(hp, pre_h, N, th, first_on ? -1 : w * th, host_base, claim + 1, &next, src0, dst0, src1, dst1,
                       dstx0, dstx1, dsty0, dsty1, cov, dstz0, dstz1);
-    copy_tiles<true>(rp, pre_r, R, tr, -1, res_base, claim, &next, src0, dst0, src1, dst1);
+    copy_tiles<true, !THIRD>(rp, pre_r, R, tr, -1, res_base, claim, &next, src0, dst0, src1, dst1);
   }
 }
 
@@ -214,7 +214,8 @@ __global__ __launch_bounds__(GT) void gather_request_kernel(GatherParams p) {
   __shared__ uint64_t src0[TILE], dst0[TILE], src1[TILE], dst1[TILE];
   request_prefix(p, pre, wtot);
   const int r = blockIdx.x;                 // Eq. 13: one worker per request
-  copy_range<false>(p, pre, pre[r], pre[r + 1], src0, dst0, src1, dst1);
+  // a request's one workgroup needs all the reads in flight it can have
+  copy_range<false, kUnroll>(p, pre, pre[r], pre[r + 1], src0, dst0, src1, dst1);
 }
 
 }  // namespace

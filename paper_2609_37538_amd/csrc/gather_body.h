@@ -13,8 +13,8 @@ constexpr int GT = kGatherThreads;
 constexpr int TILE = kGatherTile;
 constexpr int kMaxBatch = 1024;
 constexpr int kUnroll = 4;
-// Loads a thread keeps in flight for 16-byte chunks of host rows (device
-// copies and 4-byte chunks: kUnroll).  The link is full with 0.5 MB in flight,
+// Loads a thread keeps in flight for 16-byte chunks of host rows (device copies
+// and 4-byte chunks: kUnroll).  The link is full with 0.5 MB in flight,
 // and 256 workgroups have 1 MB with one load per thread; what is beyond that
 // queues before every other access of the kernel (claims, list entries, slot
 // copies): four per thread cost 16 requests 79.7 against 77.8 us and 192
@@ -156,11 +156,14 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Rows i < tn: copy chunks * sizeof(V) bytes from src[i] to dst[i] (src[i] == 0
 // skips the row), and also to dstx[i], dsty[i] and dstz[i] where those are
-// given and nonzero, with NT threads each keeping U loads in flight.
-template <typename V, int U = kUnroll, int NT = GT>
+// given and nonzero, with NT threads each keeping U loads in flight.  kOffGrid:
+// the chunks are row16 and a row's last one is at offset `last`, which may lie
+// before its place.
+template <typename V, int U = kUnroll, int NT = GT, bool kOffGrid = false>
 __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* dst, int tn,
                                           int chunks, const uint64_t* dstx = nullptr,
-                                          const uint64_t* dsty = nullptr, const uint64_t* dstz = nullptr) {
+                                          const uint64_t* dsty = nullptr, const uint64_t* dstz = nullptr,
+                                          uint32_t last = 0u) {
   const int total = tn * chunks;
   for (int q0 = threadIdx.x; q0 < total; q0 += NT * U) {
     V v[U];
@@ -171,7 +174,8 @@ __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* d
     for (int u = 0; u < U; ++u) {
       const int q = q0 + u * NT;
       const int i = q < total ? q / chunks : 0;
-      const uint64_t off = static_cast<uint64_t>(q - i * chunks) * sizeof(V);
+      uint32_t off = static_cast<uint32_t>(q - i * chunks) * static_cast<uint32_t>(sizeof(V));
+      if (kOffGrid) off = off < last ? off : last;
       const uint64_t s = src[i];
       const bool live = (q < total) & (s != 0);
       sa[u] = live ? s + off : 0;
@@ -182,31 +186,43 @@ __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* d
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (sa[u]) v[u] = load_global<V>(sa[u]);
+      if (sa[u]) v[u] = load_chunk<V, kOffGrid>(sa[u]);
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (sa[u]) {
-        store_global<V>(da[u], v[u]);
-        if (xa[u]) store_global<V>(xa[u], v[u]);
-        if (ya[u]) store_global<V>(ya[u], v[u]);
-        if (za[u]) store_global<V>(za[u], v[u]);
+        store_chunk<V, kOffGrid>(da[u], v[u]);
+        if (xa[u]) store_chunk<V, kOffGrid>(xa[u], v[u]);
+        if (ya[u]) store_chunk<V, kOffGrid>(ya[u], v[u]);
+        if (za[u]) store_chunk<V, kOffGrid>(za[u], v[u]);
       }
   }
+}
+
+// The same for rows of row_bytes bytes (below 2^32): aligned 16-byte chunks where
+// the rows are whole ones, row16 for other rows of at least 16 bytes (as 4-byte
+// chunks, 300-byte rows of 40 requests took 29.0 us per step against 28.1 and
+// 580-byte rows of 11 requests 41.7 against 41.0), 4-byte ones below.  U chunks in
+// flight per thread.  kRow16 = false leaves the row16 path out: beside the third
+// further slot of four tokens it costs whole rows more (one request 34.9
+// against 34.6 us) than it gives the others.
+template <int U, bool kRow16 = true>
+__device__ __forceinline__ void copy_rows_of(int64_t row_bytes, const uint64_t* src, const uint64_t* dst, int tn,
+                                             const uint64_t* dstx = nullptr, const uint64_t* dsty = nullptr,
+                                             const uint64_t* dstz = nullptr) {
+  if ((row_bytes & 15) == 0)
+    copy_rows<u32x4, U>(src, dst, tn, static_cast<int>(row_bytes / 16), dstx, dsty, dstz);
+  else if (kRow16 && row_bytes >= 16)
+    copy_rows<u32x4, U, GT, true>(src, dst, tn, static_cast<int>((row_bytes + 15) / 16), dstx, dsty, dstz,
+                        static_cast<uint32_t>(row_bytes - 16));
+  else
+    copy_rows<uint32_t, kUnroll>(src, dst, tn, static_cast<int>(row_bytes / 4), dstx, dsty, dstz);
 }
 
 __device__ inline void copy_tile_rows(const GatherParams& p, int tn, uint64_t* src0, uint64_t* dst0,
                                uint64_t* src1, uint64_t* dst1) {
   __syncthreads();
-  if ((p.row_bytes0 & 15) == 0)
-    copy_rows<u32x4>(src0, dst0, tn, static_cast<int>(p.row_bytes0 / 16));
-  else
-    copy_rows<uint32_t>(src0, dst0, tn, static_cast<int>(p.row_bytes0 / 4));
-  if (p.n_streams > 1) {
-    if ((p.row_bytes1 & 15) == 0)
-      copy_rows<u32x4>(src1, dst1, tn, static_cast<int>(p.row_bytes1 / 16));
-    else
-      copy_rows<uint32_t>(src1, dst1, tn, static_cast<int>(p.row_bytes1 / 4));
-  }
+  copy_rows_of<kUnroll>(p.row_bytes0, src0, dst0, tn);
+  if (p.n_streams > 1) copy_rows_of<kUnroll>(p.row_bytes1, src1, dst1, tn);
   __syncthreads();
 }
 
@@ -217,7 +233,7 @@ __device__ inline void copy_tile_rows(const GatherParams& p, int tn, uint64_t* s
 // pre[r] of request r's list (cov: rows of each request left out of the
 // batch-wide list, or none); with fixed_r >= 0, [a, b) are entries of request
 // fixed_r's own list and pre is not read.
-template <bool kDevice>
+template <bool kDevice, int U = kDevice ? kUnroll : kHostUnroll, bool kRow16 = true>
 __device__ __forceinline__ void copy_range(const GatherParams& p, const int* pre, int a, int b,
                            uint64_t* src0, uint64_t* dst0, uint64_t* src1, uint64_t* dst1,
                            uint64_t* dstx0 = nullptr, uint64_t* dstx1 = nullptr,
@@ -282,17 +298,8 @@ __device__ __forceinline__ void copy_range(const GatherParams& p, const int* pre
       }
     }
     __syncthreads();
-    if ((p.row_bytes0 & 15) == 0)
-      copy_rows<u32x4, kDevice ? kUnroll : kHostUnroll>(src0, dst0, tn, static_cast<int>(p.row_bytes0 / 16), dstx0, dsty0, dstz0);
-    else
-      copy_rows<uint32_t>(src0, dst0, tn, static_cast<int>(p.row_bytes0 / 4), dstx0, dsty0, dstz0);
-    if (p.n_streams > 1) {
-      if ((p.row_bytes1 & 15) == 0)
-        copy_rows<u32x4, kDevice ? kUnroll : kHostUnroll>(src1, dst1, tn, static_cast<int>(p.row_bytes1 / 16), dstx1,
-                                                          dsty1, dstz1);
-      else
-        copy_rows<uint32_t>(src1, dst1, tn, static_cast<int>(p.row_bytes1 / 4), dstx1, dsty1, dstz1);
-    }
+    copy_rows_of<U, kRow16>(p.row_bytes0, src0, dst0, tn, dstx0, dsty0, dstz0);
+    if (p.n_streams > 1) copy_rows_of<U, kRow16>(p.row_bytes1, src1, dst1, tn, dstx1, dsty1, dstz1);
     __syncthreads();
   }
 }
