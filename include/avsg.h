@@ -191,9 +191,12 @@ avsg_status avsg_resolve_config(const avsg_config *cfg, avsg_config *out);
  * and step, at most 2.5 MB of staging rows and tables
  * for the host rows that AVSG_GATHER_RESIDENT and AVSG_GATHER_BALANCED read
  * while Stage One runs, and with AVSG_GATHER_RESIDENT and four tokens per step
- * 4*N_q*K bytes per request and the plan's map words once more: avsg_create
- * also takes a workspace without these parts, and then reads every host row
- * after Stage One and copies the last repeats in a launch of their own).  Returns 0 for an invalid
+ * 4*N_q*K bytes per request and the plan's map words once more, and for
+ * AVSG_GATHER_BALANCED steps of one token and at most 1024 indices per request
+ * and 16384 per step 4 bytes per request: avsg_create also takes a workspace
+ * without these parts, and then reads every host row after Stage One, copies
+ * the last repeats in a launch of their own and runs small steps as two
+ * launches).  Returns 0 for an invalid
  * cfg. */
 size_t avsg_workspace_bytes(const avsg_config *cfg);
 
@@ -330,7 +333,8 @@ avsg_status avsg_export_early(avsg_handle *h, int32_t r, int32_t *n_out, int32_t
 
 /* Per-step kernel timing with HIP events recorded on the step's stream.
  * avsg_set_timing(h, 1) starts recording (and clears the record);
- * avsg_timing copies up to `cap` recorded steps (synchronizing):
+ * avsg_timing copies up to `cap` recorded steps (synchronizing; a step that
+ * otherwise runs as one launch is recorded as its two kernels):
  * match_ms[i] is the duration of step i's matching kernel, gather_ms[i] that
  * of its main Stage Two kernel (or copies), and tail_ms[i] (may be NULL) the
  * rest of Stage Two: the repeat copies of AVSG_GATHER_RESIDENT with more than

@@ -55,6 +55,8 @@ struct avsg_handle {
   int early_workers = 0;
   size_t early_list_lds = 0;
   AheadView ahead{};            // rows fetched while Stage One runs (served = 0: none)
+  uint32_t* tickets = nullptr;  // one-launch steps: [B], or none
+  int shares = 0;               // workgroups per request
   int* pipe_ctl = nullptr;      // head, tail, done, exit_count, error, last epoch
   int4* pipe_chunks = nullptr;
   int pipe_max_chunks = 0;
@@ -118,6 +120,10 @@ constexpr int64_t kAheadBytesPerToken = 256 << 10;
 constexpr int kAheadMaxTokens = 8;         // tokens that count
 constexpr int kAheadMaxRows = 64;          // rows of one workgroup
 constexpr int kAheadMaxEntries = 256;      // table entries of one workgroup
+constexpr int kShareMaxTopk = 1024;        // one-launch step: indices per request at most
+constexpr int64_t kShareMaxLookups = 16384; // and per step
+constexpr int kShareWorkgroups = 32;       // workgroups per request, fewer beyond the next line's sum
+constexpr int kShareMostWorkgroups = 128;
 
 size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -158,6 +164,7 @@ struct Layout {
   // past `total`: each used when the workspace holds it
   size_t ahead_table, ahead_rows0, ahead_rows1, with_ahead;
   size_t host_third, plan_third, with_third;
+  size_t tickets, with_tickets;
 };
 
 bool has_plan(const avsg_config& c) {
@@ -215,6 +222,27 @@ AheadView ahead_of(const avsg_config& c) {
   return a;
 }
 
+// Workgroups per request of the one-launch step (match_copy_kernel), 0 where it is
+// not taken: single-token steps of the paper's Stage Two with the default
+// workers and rows of at least 16 bytes, small enough that the chain of two
+// launches is what they cost (us per step, two launches / one: one request K =
+// 256 11.0 / 8.1, K = 512 12.2 / 9.3, K = 1024 13.8 / 11.4; 2 requests K = 1024
+// 17.2 / 15.1; 8 requests K = 256 17.5 / 14.6; 16 requests 26.4 / 21.9; 4 requests
+// K = 1024 24.9 / 22.8; 7 requests 37.3 / 35.0, 16 requests 71.2 / 68.3; 64
+// requests K = 100 31.7 / 26.5, K = 128 33.0 / 33.2).  With 2048 indices per request
+// the look-ahead fetch of the two launches gives as much (17.5 / 17.7).  16 to
+// 64 workgroups per request are alike.
+int shares_of(const avsg_config& c) {
+  if (c.match_mode != AVSG_MATCH_HASH || c.gather_mode != AVSG_GATHER_BALANCED || c.n_q != 1 ||
+      c.gather_workers != 0 || c.topk > kShareMaxTopk || static_cast<int64_t>(c.batch) * c.topk > kShareMaxLookups)
+    return 0;
+  for (int s = 0; s < c.n_streams; ++s)
+    if (c.row_bytes[s] < 16) return 0;
+  int n = kShareWorkgroups;
+  while (n > 1 && n * c.batch > kShareMostWorkgroups) n /= 2;
+  return n;
+}
+
 Layout layout_of(const avsg_config& c) {
   Layout L{};
   const size_t B = static_cast<size_t>(c.batch), S = static_cast<size_t>(c.slots);
@@ -252,6 +280,9 @@ Layout layout_of(const avsg_config& c) {
   L.plan_third = off;
   if (third) off += up(B * static_cast<size_t>(plan_map_words(c.slots, c.topk, c.n_q)) * 4);
   L.with_third = off;
+  L.tickets = off;
+  if (shares_of(c) > 0) off += up(B * 4);
+  L.with_tickets = off;
   return L;
 }
 
@@ -421,6 +452,9 @@ void bind_workspace(avsg_handle* h, unsigned char* ws, const Layout& L, size_t b
     h->ahead.stage0 = reinterpret_cast<uint64_t>(ws + L.ahead_rows0);
     h->ahead.stage1 = c.n_streams > 1 ? reinterpret_cast<uint64_t>(ws + L.ahead_rows1) : 0;
   }
+  h->tickets = nullptr;
+  h->shares = shares_of(c);
+  if (h->shares > 0 && bytes >= L.with_tickets) h->tickets = reinterpret_cast<uint32_t*>(ws + L.tickets);
   h->host_third = h->plan_third = nullptr;
   if (L.with_third > L.host_third && bytes >= L.with_third) {
     h->host_third = reinterpret_cast<int32_t*>(ws + L.host_third);
@@ -463,7 +497,7 @@ avsg_status avsg_check_config(const avsg_config* cfg) { return check_config(cfg,
 
 size_t avsg_workspace_bytes(const avsg_config* cfg) {
   if (check_config(cfg, nullptr) != AVSG_OK) return 0;
-  return layout_of(resolved(*cfg)).with_third;
+  return layout_of(resolved(*cfg)).with_tickets;
 }
 
 avsg_status avsg_resolve_config(const avsg_config* cfg, avsg_config* out) {
@@ -595,6 +629,8 @@ avsg_status avsg_create(const avsg_config* cfg, const void* const* host_rows,
     if ((e = launch_reset_dualptr(h->dp_state, B, c.topk, s)) != hipSuccess) return cleanup(AVSG_E_HIP);
   }
   if (launch_zero_u64(h->stats, static_cast<size_t>(B) * kNumStats, s) != hipSuccess)
+    return cleanup(AVSG_E_HIP);
+  if (h->tickets && launch_zero_u64(reinterpret_cast<unsigned long long*>(h->tickets), (B + 1) / 2, s) != hipSuccess)
     return cleanup(AVSG_E_HIP);
   if (hipMemcpyAsync(h->host_ptrs, h->host_dev.data(), h->host_dev.size() * 8,
                      hipMemcpyHostToDevice, s) != hipSuccess ||
@@ -789,6 +825,15 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
       p.rep_list = h->rep_list;
       p.plan_counts = h->plan_counts;
       p.plan_claim = h->plan_claim;
+    }
+    if (h->tickets && !h->timing) {   // (timed steps keep the kernels apart)
+      GatherParams g{};
+      g.B = c.batch; g.n_streams = c.n_streams; g.host_ptrs = h->host_ptrs; g.buf_ptrs = h->buf_ptrs;
+      g.row_bytes0 = c.row_bytes[0];
+      g.row_bytes1 = c.n_streams > 1 ? c.row_bytes[1] : 0;
+      HIP_TRY(h, launch_match_copy(p, g, h->tickets, h->shares, h->lds, s));
+      h->steps++;
+      return AVSG_OK;
     }
     AheadParams a{};
     a.view = h->ahead;
@@ -1259,6 +1304,7 @@ extern "C" avsg_status avsg_step_static(const avsg_config* cfg, const void* cons
   h.m = log2_exact(c.slots);
   h.cus = sd.cus;
   bind_workspace(&h, sd.ptr, L, AVSG_STATIC_SCRATCH_BYTES, h.cus);
+  h.tickets = nullptr;   // a handle zeroes them when it is made
   h.workers = c.gather_workers > 0 ? c.gather_workers : std::max(1, h.cus);
   const int max_lds = sd.max_lds;
   if (c.match_mode == AVSG_MATCH_HASH) {

@@ -252,6 +252,10 @@ size_t dualptr_lds_bytes(int K);
 
 // `ahead`: served * parts further workgroups fetch rows beside the matching ones
 hipError_t launch_match_hash(const MatchParams& p, const AheadParams& ahead, size_t lds, hipStream_t s);
+// the one-launch step of small single-token steps (K <= 1024):
+// `shares` workgroups per request; tickets[B] are 0 between steps
+hipError_t launch_match_copy(const MatchParams& p, const GatherParams& g, uint32_t* tickets, int shares, size_t lds,
+                             hipStream_t s);
 // dynamic LDS of a fetching workgroup
 size_t ahead_lds_bytes(int S, int entries, int quota);
 hipError_t prepare_match_hash(size_t lds);

@@ -556,15 +556,54 @@ __device__ __forceinline__ void plan_request(const MatchParams& p, const int r, 
   }
 }
 
+// A request's step shared by several workgroups (see match_copy_kernel): not
+// here, or workgroup `share` of `shares`.
+struct NotShared {
+  static constexpr bool on = false;
+};
+struct SharedStep {
+  static constexpr bool on = true;
+  const GatherParams* g;
+  uint32_t* ticket;   // of the request, 0 between steps
+  int share, shares;
+};
+
+// Rows [lo, hi) of the misses (index sx[k], slot so[k]) of request r, from the
+// host into their slots: every stream's chunks (row16, so rows have at least 16
+// bytes) in one pass, one read in flight per thread and round.
+template <int NT>
+__device__ __forceinline__ void copy_misses(const GatherParams& g, int r, const int32_t* sx, const int32_t* so, int lo,
+                                            int hi, uint32_t rows_u) {
+  const int c0 = static_cast<int>((g.row_bytes0 + 15) / 16);
+  const int c1 = g.n_streams > 1 ? static_cast<int>((g.row_bytes1 + 15) / 16) : 0;
+  const uint64_t h0 = g.host_ptrs[r], b0 = g.buf_ptrs[r];
+  const uint64_t h1 = c1 ? g.host_ptrs[g.B + r] : 0, b1 = c1 ? g.buf_ptrs[g.B + r] : 0;
+  const int per = c0 + c1, total = (hi - lo) * per;
+  for (int q = threadIdx.x; q < total; q += NT) {
+    const int i = q / per, ch = q - i * per;
+    const int32_t x = sx[lo + i], o = so[lo + i];
+    if (static_cast<uint32_t>(x) >= rows_u) continue;
+    const bool first = ch < c0;
+    const uint64_t rb = static_cast<uint64_t>(first ? g.row_bytes0 : g.row_bytes1);
+    const uint64_t at = static_cast<uint64_t>(first ? ch : ch - c0) * 16, off = at < rb - 16 ? at : rb - 16;
+    store_row16((first ? b0 : b1) + static_cast<uint64_t>(o) * rb + off,
+                load_row16((first ? h0 : h1) + static_cast<uint64_t>(x) * rb + off));
+  }
+}
+
 // Stage One for request r (Algorithm 4's token loop) in workgroup-owned LDS.
 // After each token with misses, publish(r, first, count) is called by every
 // thread once the token's transfer-list entries are written (a no-op for the
 // plain matching kernel).  SPT is the number of lifetimes a thread owns
 // (S / NT, at least 1) when known at compile time, so that the loops over them
 // unroll without scalar conditions; 0 takes it from S at run time.
-template <int IPT, int NT, int SPT, typename Publish>
+// Shared (one token per step): every workgroup of the request matches it in its
+// own LDS; the first writes the step's outputs and all copy their part of the
+// misses.  The table is written back, and the counters added, by the workgroup
+// whose ticket says that it was the last to read the table, so none waits.
+template <int IPT, int NT, int SPT, typename Publish, typename Shared = NotShared>
 __device__ __forceinline__ void match_request(const MatchParams& p, const int r, unsigned char* lds,
-                              Publish& publish, int* plan_counts = nullptr) {
+                              Publish& publish, int* plan_counts = nullptr, const Shared sh = Shared()) {
   constexpr int MT = NT, MW = NT / 64;
   static_assert(NT % 64 == 0 && NT <= kMatchThreads, "whole waves, at most the largest workgroup");
   // probe and chain rounds whose LDS reads are issued together: all R + 1 = 4
@@ -693,6 +732,13 @@ __device__ __forceinline__ void match_request(const MatchParams& p, const int r,
 
   __syncthreads();
 
+  bool lead = true;        // writes the step's outputs
+  uint32_t ticket = 0;     // thread 0's: how many of the request's workgroups had read the table before
+  if constexpr (Shared::on) {
+    lead = sh.share == 0;
+    if (tid == 0) ticket = atomicAdd(sh.ticket, 1u);
+  }
+
   // the first token's global pre-decay (every lifetime down by one) was
   // applied by the stage-in
   for (int g = 0; g < p.n_q; ++g) {
@@ -764,7 +810,7 @@ __device__ __forceinline__ void match_request(const MatchParams& p, const int r,
       if (found[u]) {
         if (slife[oo[u]] < 0) st_rev++;
         slife[oo[u]] = static_cast<int8_t>(L);   // refresh the hit slot
-        og[i] = oo[u];                           // a hit's output slot
+        if (lead) og[i] = oo[u];                 // a hit's output slot
         st_hits++;
       }
       if (p.hit_mask && act[u]) p.hit_mask[row * K + i] = found[u] ? 1 : 0;
@@ -798,7 +844,7 @@ __device__ __forceinline__ void match_request(const MatchParams& p, const int r,
       }
     }
     if (tid == 0) {
-      p.miss_counts[row] = n_g;
+      if (lead) p.miss_counts[row] = n_g;
       st_miss += n_g;
     }
 #pragma unroll
@@ -950,8 +996,10 @@ __device__ __forceinline__ void match_request(const MatchParams& p, const int r,
         const int k = u * MT + tid;
         sc[mo[u]] = mt[u];
         slife[mo[u]] = static_cast<int8_t>(L);
-        og[mp[u]] = mo[u];                                   // a miss's output slot
-        p.miss_list[lbase + k] = make_int2(mt[u], mo[u]);
+        if (lead) {
+          og[mp[u]] = mo[u];                                 // a miss's output slot
+          p.miss_list[lbase + k] = make_int2(mt[u], mo[u]);
+        }
         if (p.plan_list_off > 0) slist[listed + k] = static_cast<uint16_t>(mo[u]);
         if (mv[u]) {
           const uint32_t bid = kBid | (static_cast<uint32_t>(g) << 24) |
@@ -968,6 +1016,16 @@ __device__ __forceinline__ void match_request(const MatchParams& p, const int r,
       listed += n_g;
       __syncthreads();
     }
+  }
+
+  if constexpr (Shared::on) {
+    // the misses are still in rank order in smx and somiss
+    if (tid == 0) sred[3] = ticket == static_cast<uint32_t>(sh.shares - 1);
+    __syncthreads();
+    const bool last = sred[3] != 0;
+    copy_misses<NT>(*sh.g, r, smx, somiss, listed * sh.share / sh.shares, listed * (sh.share + 1) / sh.shares, rows_u);
+    if (!last) return;
+    if (tid == 0) *sh.ticket = 0;   // for the next step
   }
 
   // installs of the last token that lost their bucket: of the bids it made,

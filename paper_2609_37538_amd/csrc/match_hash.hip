@@ -59,6 +59,25 @@ __global__ __launch_bounds__(NT) void match_hash_kernel(MatchParams p, AheadPara
   match_request<IPT, NT, SPT>(p, static_cast<int>(blockIdx.x), lds, none);
 }
 
+// A small single-token step of the paper's Stage Two (S3) in one launch: every
+// request has `shares` workgroups, each of which runs Stage One for the request
+// by itself (the same result in each one's LDS) and then copies its consecutive
+// part of the misses, floor/ceil(n / shares) of them.  As two launches such a
+// step is a chain of latencies: the second launch starts 1.2 us after the first
+// one's last store, and reads counts, list and addresses before its first row
+// read; here the row reads follow Stage One's last barrier, before the table is
+// written back.  Reading the table `shares` times costs nothing that shows (it
+// comes from L2), and nothing waits for another workgroup (tickets, see
+// match_request).
+template <int IPT, int NT, int SPT>
+__global__ __launch_bounds__(NT) void match_copy_kernel(MatchParams p, GatherParams g, uint32_t* tickets, int shares) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int r = static_cast<int>(blockIdx.x) / shares;
+  NoPublish none;
+  match_request<IPT, NT, SPT>(p, r, lds, none, nullptr,
+                              SharedStep{&g, tickets + r, static_cast<int>(blockIdx.x) - r * shares, shares});
+}
+
 __global__ void reset_tables_kernel(int32_t* c, uint32_t* q, size_t n) {
   for (size_t j = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; j < n;
        j += static_cast<size_t>(gridDim.x) * blockDim.x) {
@@ -270,58 +289,63 @@ size_t stage_one_lds_bytes(int S, int K, int n_q, bool plan) {
 }
 
 // The instantiations: lifetimes per thread S / NT is a power of two up to 16
-// with 1024 threads (S <= 16384) and up to 4 with 256 (S <= 1024).
-template <int IPT, int NT>
+// with 1024 threads (S <= 16384) and up to 4 with 256 (S <= 1024).  kCopy: the
+// one-launch step, for up to 1024 indices per request.
+template <bool kCopy, int IPT, int NT, int SPT>
+static const void* match_instance() {
+  if constexpr (kCopy) return reinterpret_cast<const void*>(&match_copy_kernel<IPT, NT, SPT>);
+  else return reinterpret_cast<const void*>(&match_hash_kernel<IPT, NT, SPT>);
+}
+
+template <bool kCopy, int IPT, int NT>
 static const void* match_kernel_for(int spt) {
   switch (spt) {
-    case 1: return reinterpret_cast<const void*>(&match_hash_kernel<IPT, NT, 1>);
-    case 2: return reinterpret_cast<const void*>(&match_hash_kernel<IPT, NT, 2>);
-    case 4: return reinterpret_cast<const void*>(&match_hash_kernel<IPT, NT, 4>);
+    case 1: return match_instance<kCopy, IPT, NT, 1>();
+    case 2: return match_instance<kCopy, IPT, NT, 2>();
+    case 4: return match_instance<kCopy, IPT, NT, 4>();
     default: break;
   }
   if constexpr (NT == kMatchThreads) {
-    if (spt == 8) return reinterpret_cast<const void*>(&match_hash_kernel<IPT, NT, 8>);
-    if (spt == 16) return reinterpret_cast<const void*>(&match_hash_kernel<IPT, NT, 16>);
+    if (spt == 8) return match_instance<kCopy, IPT, NT, 8>();
+    if (spt == 16) return match_instance<kCopy, IPT, NT, 16>();
   }
   return nullptr;
 }
 
-static const void* match_kernel(int S, int K) {
-  const int nt = match_threads(S, K), ipt = ipt_for(S, K), spt = S >= nt ? S / nt : 1;
+template <bool kCopy>
+static const void* match_kernel_of(int nt, int ipt, int spt) {
   if (nt == kSmallThreads) {
     switch (ipt) {
-      case 1: return match_kernel_for<1, kSmallThreads>(spt);
-      case 2: return match_kernel_for<2, kSmallThreads>(spt);
+      case 1: return match_kernel_for<kCopy, 1, kSmallThreads>(spt);
+      case 2: return match_kernel_for<kCopy, 2, kSmallThreads>(spt);
       default: return nullptr;
     }
   }
-  switch (ipt) {
-    case 1: return match_kernel_for<1, kMatchThreads>(spt);
-    case 2: return match_kernel_for<2, kMatchThreads>(spt);
-    case 3: return match_kernel_for<3, kMatchThreads>(spt);
-    case 4: return match_kernel_for<4, kMatchThreads>(spt);
-    default: return nullptr;
+  if (ipt == 1) return match_kernel_for<kCopy, 1, kMatchThreads>(spt);
+  if constexpr (!kCopy) {
+    if (ipt == 2) return match_kernel_for<false, 2, kMatchThreads>(spt);
+    if (ipt == 3) return match_kernel_for<false, 3, kMatchThreads>(spt);
+    if (ipt == 4) return match_kernel_for<false, 4, kMatchThreads>(spt);
   }
+  return nullptr;
+}
+
+template <bool kCopy>
+static const void* match_kernel(int S, int K) {
+  const int nt = match_threads(S, K);
+  return match_kernel_of<kCopy>(nt, ipt_for(S, K), S >= nt ? S / nt : 1);
 }
 
 hipError_t prepare_match_hash(size_t lds) {
-  static const int spts[] = {1, 2, 4, 8, 16};
-  for (int ipt = 1; ipt <= kMaxIPT; ++ipt)
-    for (int spt : spts) {
-      const void* k[2] = {nullptr, nullptr};
-      switch (ipt) {
-        case 1: k[0] = match_kernel_for<1, kMatchThreads>(spt); k[1] = match_kernel_for<1, kSmallThreads>(spt); break;
-        case 2: k[0] = match_kernel_for<2, kMatchThreads>(spt); k[1] = match_kernel_for<2, kSmallThreads>(spt); break;
-        case 3: k[0] = match_kernel_for<3, kMatchThreads>(spt); break;
-        case 4: k[0] = match_kernel_for<4, kMatchThreads>(spt); break;
-        default: break;
-      }
-      for (const void* f : k) {
-        if (!f) continue;
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-        if (e != hipSuccess) return e;
-      }
-    }
+  for (int nt : {kSmallThreads, kMatchThreads})
+    for (int ipt = 1; ipt <= kMaxIPT; ++ipt)
+      for (int spt : {1, 2, 4, 8, 16})
+        for (const void* f : {match_kernel_of<false>(nt, ipt, spt), match_kernel_of<true>(nt, ipt, spt)}) {
+          if (!f) continue;
+          const hipError_t e =
+              hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+          if (e != hipSuccess) return e;
+        }
   return hipSuccess;
 }
 
@@ -330,13 +354,24 @@ size_t ahead_lds_bytes(int S, int entries, int quota) {
 }
 
 hipError_t launch_match_hash(const MatchParams& p, const AheadParams& ahead, size_t lds, hipStream_t s) {
-  const void* f = match_kernel(p.S, p.K);
+  const void* f = match_kernel<false>(p.S, p.K);
   if (!f) return hipErrorInvalidValue;
   MatchParams args = p;
   AheadParams aargs = ahead;
   void* argv[] = {&args, &aargs};
   const unsigned extra = static_cast<unsigned>(ahead.view.served * ahead.view.parts);
   return hipLaunchKernel(f, dim3(static_cast<unsigned>(p.B) + extra), dim3(match_threads(p.S, p.K)), argv, lds, s);
+}
+
+hipError_t launch_match_copy(const MatchParams& p, const GatherParams& g, uint32_t* tickets, int shares, size_t lds,
+                             hipStream_t s) {
+  const void* f = match_kernel<true>(p.S, p.K);
+  if (!f || shares < 1 || p.n_q != 1) return hipErrorInvalidValue;
+  MatchParams margs = p;
+  GatherParams gargs = g;
+  void* argv[] = {&margs, &gargs, &tickets, &shares};
+  return hipLaunchKernel(f, dim3(static_cast<unsigned>(p.B) * static_cast<unsigned>(shares)),
+                         dim3(match_threads(p.S, p.K)), argv, lds, s);
 }
 
 hipError_t launch_reset_tables(int32_t* c, uint32_t* q, size_t n, hipStream_t s) {
