@@ -826,7 +826,9 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
       p.plan_counts = h->plan_counts;
       p.plan_claim = h->plan_claim;
     }
-    if (h->tickets && !h->timing) {   // (timed steps keep the kernels apart)
+    // (timed steps keep the kernels apart; slots written over the selections
+    // would be read as such by the request's other workgroups)
+    if (h->tickets && !h->timing && d_slots != d_topk) {
       GatherParams g{};
       g.B = c.batch; g.n_streams = c.n_streams; g.host_ptrs = h->host_ptrs; g.buf_ptrs = h->buf_ptrs;
       g.row_bytes0 = c.row_bytes[0];

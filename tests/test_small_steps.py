@@ -94,3 +94,29 @@ def test_small_step_timing_and_short_workspace():
         A.avsg_destroy(h)
         op.close()
         host.free()
+
+
+def test_small_step_in_place():
+    """Slots written over the step's own selections."""
+    from paper_2609_37538_amd import avsg as A
+    import torch
+    spec = W.custom_spec(name="small_in_place", batch=2, topk=512, slots=2048, n_q=1, steps=6, ctx=9000,
+                         retention=0.7)
+    wl = W.Workload(spec)
+    host = HostRows(wl)
+    orc = OracleSide(wl, host)
+    cfg = A.make_config(spec.batch, spec.topk, spec.n_q, spec.slots, row_bytes=spec.row_bytes)
+    op = A.Operator(cfg, host.ptrs, wl.ctx)
+    try:
+        for t in range(spec.steps):
+            X = wl.topk(t)
+            Xd = torch.from_numpy(np.ascontiguousarray(X, dtype=np.int32)).cuda()
+            torch.cuda.synchronize()
+            A.avsg_step(op.h, Xd.data_ptr(), None, Xd.data_ptr(), op.miss_counts.data_ptr(), op.stream.cuda_stream)
+            torch.cuda.synchronize()
+            O_ref, n_ref = orc.step(X, None)
+            compare_step(t, O_ref, n_ref, Xd.cpu().numpy(), op.miss_counts.cpu().numpy())
+            assert np.array_equal(op.buffers[0].cpu().numpy(), orc.images[0]), f"step {t}"
+    finally:
+        op.close()
+        host.free()
