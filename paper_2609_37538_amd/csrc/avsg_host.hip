@@ -122,6 +122,7 @@ constexpr int kAheadMaxRows = 64;          // rows of one workgroup
 constexpr int kAheadMaxEntries = 256;      // table entries of one workgroup
 constexpr int kShareMaxTopk = 1024;        // one-launch step: indices per request at most
 constexpr int64_t kShareMaxLookups = 16384; // and per step
+constexpr int64_t kShareMaxRowBytes = 64 << 10; // its chunks of all misses are counted in 32 bits
 constexpr int kShareWorkgroups = 32;       // workgroups per request, fewer beyond the next line's sum
 constexpr int kShareMostWorkgroups = 128;
 
@@ -224,7 +225,7 @@ AheadView ahead_of(const avsg_config& c) {
 
 // Workgroups per request of the one-launch step (match_copy_kernel), 0 where it is
 // not taken: single-token steps of the paper's Stage Two with the default
-// workers and rows of at least 16 bytes, small enough that the chain of two
+// workers and rows of 16 bytes to 64 KiB, small enough that the chain of two
 // launches is what they cost (us per step, two launches / one: one request K =
 // 256 11.0 / 8.1, K = 512 12.2 / 9.3, K = 1024 13.8 / 11.4; 2 requests K = 1024
 // 17.2 / 15.1; 8 requests K = 256 17.5 / 14.6; 16 requests 26.4 / 21.9; 4 requests
@@ -237,7 +238,7 @@ int shares_of(const avsg_config& c) {
       c.gather_workers != 0 || c.topk > kShareMaxTopk || static_cast<int64_t>(c.batch) * c.topk > kShareMaxLookups)
     return 0;
   for (int s = 0; s < c.n_streams; ++s)
-    if (c.row_bytes[s] < 16) return 0;
+    if (c.row_bytes[s] < 16 || c.row_bytes[s] > kShareMaxRowBytes) return 0;
   int n = kShareWorkgroups;
   while (n > 1 && n * c.batch > kShareMostWorkgroups) n /= 2;
   return n;
@@ -827,8 +828,11 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
       p.plan_claim = h->plan_claim;
     }
     // (timed steps keep the kernels apart; slots written over the selections
-    // would be read as such by the request's other workgroups)
-    if (h->tickets && !h->timing && d_slots != d_topk) {
+    // would be read as such by the request's other workgroups, also where the
+    // two overlap in part only)
+    const uintptr_t tk = reinterpret_cast<uintptr_t>(d_topk), sl = reinterpret_cast<uintptr_t>(d_slots);
+    const uintptr_t span = static_cast<uintptr_t>(c.batch) * c.topk * sizeof(int32_t);
+    if (h->tickets && !h->timing && (sl >= tk + span || tk >= sl + span)) {
       GatherParams g{};
       g.B = c.batch; g.n_streams = c.n_streams; g.host_ptrs = h->host_ptrs; g.buf_ptrs = h->buf_ptrs;
       g.row_bytes0 = c.row_bytes[0];

@@ -96,11 +96,13 @@ def test_small_step_timing_and_short_workspace():
         host.free()
 
 
-def test_small_step_in_place():
-    """Slots written over the step's own selections."""
+@pytest.mark.parametrize("ahead", [0, 128])
+def test_small_step_in_place(ahead):
+    """Slots written over the step's own selections, or `ahead` values before
+    them (one request then, so that no request writes another's selections)."""
     from paper_2609_37538_amd import avsg as A
     import torch
-    spec = W.custom_spec(name="small_in_place", batch=2, topk=512, slots=2048, n_q=1, steps=6, ctx=9000,
+    spec = W.custom_spec(name="small_in_place", batch=1 if ahead else 2, topk=512, slots=2048, n_q=1, steps=6, ctx=9000,
                          retention=0.7)
     wl = W.Workload(spec)
     host = HostRows(wl)
@@ -110,12 +112,14 @@ def test_small_step_in_place():
     try:
         for t in range(spec.steps):
             X = wl.topk(t)
-            Xd = torch.from_numpy(np.ascontiguousarray(X, dtype=np.int32)).cuda()
+            both = torch.zeros(X.size + ahead, dtype=torch.int32, device="cuda")
+            Xd, Od = both[ahead:], both[:X.size]
+            Xd.copy_(torch.from_numpy(np.ascontiguousarray(X, dtype=np.int32)).view(-1))
             torch.cuda.synchronize()
-            A.avsg_step(op.h, Xd.data_ptr(), None, Xd.data_ptr(), op.miss_counts.data_ptr(), op.stream.cuda_stream)
+            A.avsg_step(op.h, Xd.data_ptr(), None, Od.data_ptr(), op.miss_counts.data_ptr(), op.stream.cuda_stream)
             torch.cuda.synchronize()
             O_ref, n_ref = orc.step(X, None)
-            compare_step(t, O_ref, n_ref, Xd.cpu().numpy(), op.miss_counts.cpu().numpy())
+            compare_step(t, O_ref, n_ref, Od.view(X.shape).cpu().numpy(), op.miss_counts.cpu().numpy())
             assert np.array_equal(op.buffers[0].cpu().numpy(), orc.images[0]), f"step {t}"
     finally:
         op.close()
