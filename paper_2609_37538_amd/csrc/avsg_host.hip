@@ -728,6 +728,23 @@ static avsg_status sdma_gather(avsg_handle* h, const int32_t* d_counts, hipStrea
   return AVSG_OK;
 }
 
+// Whether no output of a single-token step overlaps one of its inputs, also in
+// part.  In a one-launch step one workgroup of a request writes the outputs
+// while the request's others may still read the inputs; as two launches a
+// request's one matching workgroup has read its inputs before it writes.
+static bool outputs_apart(const avsg_config& c, const int32_t* d_topk, const int64_t* d_verified_len,
+                          const int32_t* d_slots, const int32_t* d_miss_counts) {
+  const size_t B = static_cast<size_t>(c.batch), K = static_cast<size_t>(c.topk);
+  auto apart = [](const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return !b || x >= y + nb || y >= x + na;
+  };
+  auto from_inputs = [&](const void* out, size_t n) {
+    return apart(out, n, d_topk, B * K * sizeof(int32_t)) && apart(out, n, d_verified_len, B * sizeof(int64_t));
+  };
+  return from_inputs(d_slots, B * K * sizeof(int32_t)) && from_inputs(d_miss_counts, B * sizeof(int32_t));
+}
+
 // The kernels of one decode step for the handle's configuration, enqueued on s.
 static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int64_t* d_verified_len,
                                 int32_t* d_slots, int32_t* d_miss_counts, hipStream_t s) {
@@ -827,12 +844,8 @@ static avsg_status enqueue_step(avsg_handle* h, const int32_t* d_topk, const int
       p.plan_counts = h->plan_counts;
       p.plan_claim = h->plan_claim;
     }
-    // (timed steps keep the kernels apart; slots written over the selections
-    // would be read as such by the request's other workgroups, also where the
-    // two overlap in part only)
-    const uintptr_t tk = reinterpret_cast<uintptr_t>(d_topk), sl = reinterpret_cast<uintptr_t>(d_slots);
-    const uintptr_t span = static_cast<uintptr_t>(c.batch) * c.topk * sizeof(int32_t);
-    if (h->tickets && !h->timing && (sl >= tk + span || tk >= sl + span)) {
+    // (timed steps keep the kernels apart)
+    if (h->tickets && !h->timing && outputs_apart(c, d_topk, d_verified_len, d_slots, d_miss_counts)) {
       GatherParams g{};
       g.B = c.batch; g.n_streams = c.n_streams; g.host_ptrs = h->host_ptrs; g.buf_ptrs = h->buf_ptrs;
       g.row_bytes0 = c.row_bytes[0];
