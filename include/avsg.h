@@ -61,7 +61,10 @@ typedef int32_t avsg_status;
 #define AVSG_MATCH_DUALPTR 1  /* scalar dual-pointer sort-merge baseline, needs S == K (Appendix C) */
 
 /* Stage Two work assignment (Appendix D). */
-#define AVSG_GATHER_BALANCED 0 /* S3: the miss list split into floor/ceil(N_miss/C) consecutive misses per worker (Eq. 6) */
+#define AVSG_GATHER_BALANCED 0 /* S3: the miss list split into floor/ceil(N_miss/C) consecutive misses per worker (Eq. 6);
+                                  with one token per step, at most 1024 indices per request and 16384 per step
+                                  and gather_workers 0, a small step runs as one launch instead, in which
+                                  each request's misses are split the same way over workgroups of its own */
 #define AVSG_GATHER_REQUEST 1  /* S1: one worker per request (Eq. 13) */
 #define AVSG_GATHER_SDMA 2     /* comparator: the miss list is read back and every missed row is one hipMemcpyAsync on the copy engines */
 #define AVSG_GATHER_NONE 3     /* Stage One only (matching measured alone) */

@@ -122,9 +122,10 @@ constexpr int kAheadMaxRows = 64;          // rows of one workgroup
 constexpr int kAheadMaxEntries = 256;      // table entries of one workgroup
 constexpr int kShareMaxTopk = 1024;        // one-launch step: indices per request at most
 constexpr int64_t kShareMaxLookups = 16384; // and per step
-constexpr int64_t kShareMaxRowBytes = 64 << 10; // its chunks of all misses are counted in 32 bits
-constexpr int kShareWorkgroups = 32;       // workgroups per request, fewer beyond the next line's sum
+constexpr int kShareWorkgroups = 32;       // workgroups per request, fewer beyond the next line's sum ...
 constexpr int kShareMostWorkgroups = 128;
+constexpr int kShareRounds = 10;           // ... unless a request would need more rounds of reads than this,
+constexpr int kShareAllThreads = 224 * 1024;   // and two launches where the step would need more threads
 
 size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -225,23 +226,38 @@ AheadView ahead_of(const avsg_config& c) {
 
 // Workgroups per request of the one-launch step (match_copy_kernel), 0 where it is
 // not taken: single-token steps of the paper's Stage Two with the default
-// workers and rows of 16 bytes to 64 KiB, small enough that the chain of two
-// launches is what they cost (us per step, two launches / one: one request K =
-// 256 11.0 / 8.1, K = 512 12.2 / 9.3, K = 1024 13.8 / 11.4; 2 requests K = 1024
-// 17.2 / 15.1; 8 requests K = 256 17.5 / 14.6; 16 requests 26.4 / 21.9; 4 requests
-// K = 1024 24.9 / 22.8; 7 requests 37.3 / 35.0, 16 requests 71.2 / 68.3; 64
-// requests K = 100 31.7 / 26.5, K = 128 33.0 / 33.2).  With 2048 indices per request
-// the look-ahead fetch of the two launches gives as much (17.5 / 17.7).  16 to
-// 64 workgroups per request are alike.
+// workers and rows of at least 16 bytes, small enough that the chain of two
+// launches is what they cost.  A request's misses are copied by its own
+// workgroups alone, so they must be able to copy a request that misses
+// everything (one that has just started, beside others that hardly miss) no
+// slower than all CUs do in a launch of their own: within ten rounds of one
+// 16-byte read per thread.  Us per step, two launches / one, 1152-byte rows, all
+// requests with a tenth of misses, then one of them with nothing but misses:
+// one request K = 256 10.2 / 6.9, 15.6 / 13.5; K = 1024 11.3 / 9.3, 32.9 / 30.6;
+// 8 requests K = 1024 23.9 / 21.4, 69.0 / 65.0; 33 requests K = 256 48.4 / 41.6,
+// 56.7 / 52.8 (with two workgroups per request, all that 128 leave it, 83.4);
+// 64 requests K = 100 38.6 / 32.0, 42.1 / 40.6 (two each: 47.7); 128 requests
+// K = 128 81.7 / 75.5, 85.4 / 84.7 (one each: 112.3).  One request of K = 512 in
+// 1024 slots 11.7 / 10.6, 20.0 / 20.7.  With 2048 indices per request the
+// look-ahead fetch of the two launches gives as much (17.5 / 17.7).  Beyond
+// 224K threads their reads queue (all missing: 12 requests K = 674 of 4096-byte
+// rows 487 / 501 with 384K, 1024 requests K = 16 355 / 372 with 256K; 28
+// requests K = 529 388 / 388 with 224K).
 int shares_of(const avsg_config& c) {
   if (c.match_mode != AVSG_MATCH_HASH || c.gather_mode != AVSG_GATHER_BALANCED || c.n_q != 1 ||
       c.gather_workers != 0 || c.topk > kShareMaxTopk || static_cast<int64_t>(c.batch) * c.topk > kShareMaxLookups)
     return 0;
-  for (int s = 0; s < c.n_streams; ++s)
-    if (c.row_bytes[s] < 16 || c.row_bytes[s] > kShareMaxRowBytes) return 0;
+  int64_t chunks = 0;   // of a row of every stream
+  for (int s = 0; s < c.n_streams; ++s) {
+    if (c.row_bytes[s] < 16) return 0;
+    chunks += (c.row_bytes[s] + 15) / 16;
+  }
+  const int threads = match_threads(c.slots, c.topk);
+  auto in_rounds = [&](int n) { return (c.topk + n - 1) / n * chunks <= kShareRounds * threads; };
   int n = kShareWorkgroups;
   while (n > 1 && n * c.batch > kShareMostWorkgroups) n /= 2;
-  return n;
+  while (n < kShareWorkgroups && !in_rounds(n)) n *= 2;
+  return in_rounds(n) && n * c.batch * threads <= kShareAllThreads ? n : 0;
 }
 
 Layout layout_of(const avsg_config& c) {
