@@ -228,8 +228,8 @@ struct PlanHash {
 constexpr uint32_t kFanSlot = 0x7FFFu;
 constexpr uint32_t kFanMore = 0x80000000u;
 // Bids v; returns the bid that is now in neither field (0 = none): v itself or
-// the one it displaced.  With N_q <= 4 a word gets at most three bids, so at
-// most one call of its bids returns nonzero.
+// the one it displaced.  With N_q <= 4 and no index twice in a token a word gets
+// at most three bids, so at most one call of its bids returns nonzero.
 __device__ __forceinline__ uint32_t fan_bid(uint32_t* w, uint32_t v) {
   uint32_t cur = *w;
   for (;;) {
@@ -284,7 +284,9 @@ __device__ __forceinline__ int plan_lookup(const uint32_t* smp, const int32_t* s
 // the index), so with up to three tokens per step no repeat is left for a
 // later copy; with four tokens the one repeat that can be left is kept beside
 // the fan slots in device memory (host_third) for the same copy, and listed as
-// a repeat all the same.  The lists keep transfer-list order.  LDS: a map of P words,
+// a repeat all the same.  (An index repeated within a token, which the caller
+// must not pass, can leave further ones, and no later copy runs then: they are
+// host copies of their own.)  The lists keep transfer-list order.  LDS: a map of P words,
 // open addressing with linear probing keyed by the index a word names through
 // c[]; a word is (resident bit | early bit | tag | slot + 1), 0 = free, and
 // atomicMax makes every choice deterministic; beside it P fan words, one per
@@ -507,9 +509,11 @@ __device__ __forceinline__ void plan_request(const MatchParams& p, const int r, 
       if (p.plan_third && (fw & kFanMore)) further = third[c.hw];
     }
     if (c.kind == 2) {
-      ++n_rep;
       const int2 f = fan_slots(sfan[c.hw]);
       if (f.x == c.v.y || f.y == c.v.y) c.kind = 3;   // written by the host copy
+      // a repeat that nothing else writes (see above): read from the host again
+      else if (p.plan_third && third[c.hw] != c.v.y) c.kind = 0;
+      n_rep += c.kind != 0 ? 1 : 0;
     }
     if (c.kind == 5) ++n_rep;             // filled by the early fetch's copy of its index
     const int kind = c.kind;

@@ -73,3 +73,35 @@ def test_repeats_of_four_tokens(name, kw, short):
     finally:
         op.close()
         host.free()
+
+
+@pytest.mark.parametrize("copies", [2, 5])
+def test_index_repeated_within_a_token(copies):
+    """An index repeated within a token is the caller's error, but every slot
+    that a miss reserved still gets its row: buffers equal those of the
+    transfer that reads each miss from the host."""
+    from paper_2609_37538_amd import avsg as A
+    import torch
+    spec = W.custom_spec(name=f"four_repeated_{copies}", batch=3, topk=120, slots=512, n_q=4, steps=6, ctx=3000,
+                         retention=0.6, row_bytes=(1152, 132))
+    wl = W.Workload(spec)
+    host = HostRows(wl)
+    ops = [A.Operator(A.make_config(spec.batch, spec.topk, spec.n_q, spec.slots, retry=0, row_bytes=spec.row_bytes,
+                                    gather_mode=mode), host.ptrs, wl.ctx)
+           for mode in (A.AVSG_GATHER_BALANCED, A.AVSG_GATHER_RESIDENT)]
+    try:
+        for t in range(spec.steps):
+            X = wl.topk(t).copy()
+            X[:, :, : 12 * copies] = np.repeat(X[:, :1, :12], copies, axis=2)   # the same twelve in every token
+            Xd = torch.from_numpy(np.ascontiguousarray(X, dtype=np.int32)).cuda()
+            out = [op.step(Xd) for op in ops]
+            torch.cuda.synchronize()
+            assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]), f"step {t}"
+            for s in range(len(spec.row_bytes)):
+                assert torch.equal(ops[0].buffers[s], ops[1].buffers[s]), f"step {t} stream {s}"
+        a, b = (op.stats() for op in ops)
+        assert a["misses"] == b["misses"] and b["duplicate_rows"] > 0 and b["host_bytes"] < a["host_bytes"]
+    finally:
+        for op in ops:
+            op.close()
+        host.free()
