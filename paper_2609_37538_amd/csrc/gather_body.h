@@ -163,7 +163,7 @@ template <typename V, int U = kUnroll, int NT = GT, bool kOffGrid = false>
 __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* dst, int tn,
                                           int chunks, const uint64_t* dstx = nullptr,
                                           const uint64_t* dsty = nullptr, const uint64_t* dstz = nullptr,
-                                          uint32_t last = 0u) {
+                                          uint64_t last = 0u) {
   const int total = tn * chunks;
   for (int q0 = threadIdx.x; q0 < total; q0 += NT * U) {
     V v[U];
@@ -174,7 +174,7 @@ __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* d
     for (int u = 0; u < U; ++u) {
       const int q = q0 + u * NT;
       const int i = q < total ? q / chunks : 0;
-      uint32_t off = static_cast<uint32_t>(q - i * chunks) * static_cast<uint32_t>(sizeof(V));
+      uint64_t off = static_cast<uint64_t>(static_cast<uint32_t>(q - i * chunks)) * sizeof(V);
       if (kOffGrid) off = off < last ? off : last;
       const uint64_t s = src[i];
       const bool live = (q < total) & (s != 0);
@@ -198,7 +198,7 @@ __device__ __forceinline__ void copy_rows(const uint64_t* src, const uint64_t* d
   }
 }
 
-// The same for rows of row_bytes bytes (below 2^32): aligned 16-byte chunks where
+// The same for rows of row_bytes bytes: aligned 16-byte chunks where
 // the rows are whole ones, row16 for other rows of at least 16 bytes (as 4-byte
 // chunks, 300-byte rows of 40 requests took 29.0 us per step against 28.1 and
 // 580-byte rows of 11 requests 41.7 against 41.0), 4-byte ones below.  U chunks in
@@ -213,7 +213,7 @@ __device__ __forceinline__ void copy_rows_of(int64_t row_bytes, const uint64_t* 
     copy_rows<u32x4, U>(src, dst, tn, static_cast<int>(row_bytes / 16), dstx, dsty, dstz);
   else if (kRow16 && row_bytes >= 16)
     copy_rows<u32x4, U, GT, true>(src, dst, tn, static_cast<int>((row_bytes + 15) / 16), dstx, dsty, dstz,
-                        static_cast<uint32_t>(row_bytes - 16));
+                        static_cast<uint64_t>(row_bytes - 16));
   else
     copy_rows<uint32_t, kUnroll>(src, dst, tn, static_cast<int>(row_bytes / 4), dstx, dsty, dstz);
 }
