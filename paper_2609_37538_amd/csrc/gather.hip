@@ -182,7 +182,9 @@ __global__ __launch_bounds__(GT) void copy_device_kernel(GatherParams p) {
   copy_range<true>(p, pre, a, b, src0, dst0, src1, dst1);
 }
 
+static_assert(TILE <= 64, "the first wave stages a tile");
 __global__ __launch_bounds__(GT) void gather_position_kernel(GatherParams p) {
+  __shared__ int live;
   __shared__ uint64_t src0[TILE], dst0[TILE], src1[TILE], dst1[TILE];
   const long long per_req = static_cast<long long>(p.n_q) * p.K;
   const long long P = per_req * p.B;
@@ -198,6 +200,8 @@ __global__ __launch_bounds__(GT) void gather_position_kernel(GatherParams p) {
       const int32_t o = p.slots[pos];
       const bool miss = p.hit_mask[pos] == 0;
       const bool ok = miss && x >= 0 && static_cast<int64_t>(x) < p.rows[r] && o >= 0 && o < p.S;
+      const int alive = __popcll(__ballot(ok));   // a tile is staged by one wave
+      if (i == 0) live = alive;
       src0[i] = ok ? p.host_ptrs[r] + static_cast<uint64_t>(x) * p.row_bytes0 : 0;
       dst0[i] = p.buf_ptrs[r] + static_cast<uint64_t>(o) * p.row_bytes0;
       if (p.n_streams > 1) {
@@ -205,17 +209,18 @@ __global__ __launch_bounds__(GT) void gather_position_kernel(GatherParams p) {
         dst1[i] = p.buf_ptrs[p.B + r] + static_cast<uint64_t>(o) * p.row_bytes1;
       }
     }
-    copy_tile_rows(p, tn, src0, dst0, src1, dst1);
+    __syncthreads();
+    copy_tile_rows(p, tn, src0, dst0, src1, dst1, C <= kDeepWorkgroups || live * 4 <= tn);
   }
 }
 
+template <int U>
 __global__ __launch_bounds__(GT) void gather_request_kernel(GatherParams p) {
   __shared__ int pre[kMaxBatch + 1], wtot[GT / 64];
   __shared__ uint64_t src0[TILE], dst0[TILE], src1[TILE], dst1[TILE];
   request_prefix(p, pre, wtot);
   const int r = blockIdx.x;                 // Eq. 13: one worker per request
-  // a request's one workgroup needs all the reads in flight it can have
-  copy_range<false, kUnroll>(p, pre, pre[r], pre[r + 1], src0, dst0, src1, dst1);
+  copy_range<false, U>(p, pre, pre[r], pre[r + 1], src0, dst0, src1, dst1);
 }
 
 }  // namespace
@@ -250,7 +255,10 @@ hipError_t launch_gather_position(const GatherParams& p, int workers, hipStream_
 
 hipError_t launch_gather_request(const GatherParams& p, hipStream_t s) {
   if (p.B > kMaxBatch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gather_request_kernel, dim3(p.B), dim3(GT), 0, s, p);
+  if (p.B <= kDeepWorkgroups)
+    hipLaunchKernelGGL(gather_request_kernel<kUnroll>, dim3(p.B), dim3(GT), 0, s, p);
+  else
+    hipLaunchKernelGGL(gather_request_kernel<kHostUnroll>, dim3(p.B), dim3(GT), 0, s, p);
   return hipGetLastError();
 }
 

@@ -13,13 +13,26 @@ constexpr int GT = kGatherThreads;
 constexpr int TILE = kGatherTile;
 constexpr int kMaxBatch = 1024;
 constexpr int kUnroll = 4;
-// Loads a thread keeps in flight for 16-byte chunks of host rows (device copies
-// and 4-byte chunks: kUnroll).  The link is full with 0.5 MB in flight,
-// and 256 workgroups have 1 MB with one load per thread; what is beyond that
-// queues before every other access of the kernel (claims, list entries, slot
-// copies): four per thread cost 16 requests 79.7 against 77.8 us and 192
-// requests with high reuse 70.9 against 69.0.
+// Loads a thread keeps in flight for 16-byte chunks of host rows in the balanced
+// and resident gathers (device copies and 4-byte chunks: kUnroll).  The link is
+// full with 0.5 MB in flight, and 256 workgroups have 1 MB with one load per
+// thread; what is beyond that queues before every other access of the kernel
+// (claims, list entries, slot copies): four per thread cost 16 requests 79.7
+// against 77.8 us and 192 requests with high reuse 70.9 against 69.0.  With few
+// workers one load is no loss against four through flat accesses, which wait
+// for one another (16 requests, 4, 16 and 64 workers: 270, 89.8 and 65.6 us
+// per step against 290, 89.0 and 70.8).
 constexpr int kHostUnroll = 1;
+// The request and position gathers keep kUnroll in flight with at most this many
+// workgroups, and the position gather also where at most a quarter of a tile
+// misses (the lanes of a hit read nothing).  All misses, us per step with four
+// loads per thread and with one: request gather, 16 requests 182 / 233, 64
+// requests 679 / 707, 128 requests 1347 / 1347, 200 requests 2167 / 2092, 400
+// requests 2188 / 2098 (24 to 40 requests are 1-4% slower with four, and 7-9%
+// faster where a tenth misses); position gather, 16 workers 481 / 647, 128
+// workers 366 / 384, 256 workers with one request 71.0 / 61.2, with 48 requests
+// 540 / 514; a tenth of misses, 256 workers with 16 requests 26.3 / 27.9.
+constexpr int kDeepWorkgroups = 128;
 
 __device__ __forceinline__ int lane_index() {
   return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -218,11 +231,15 @@ __device__ __forceinline__ void copy_rows_of(int64_t row_bytes, const uint64_t* 
     copy_rows<uint32_t, kUnroll>(src, dst, tn, static_cast<int>(row_bytes / 4), dstx, dsty, dstz);
 }
 
+// Rows of a staged tile; deep: kUnroll reads in flight per thread.
 __device__ inline void copy_tile_rows(const GatherParams& p, int tn, uint64_t* src0, uint64_t* dst0,
-                               uint64_t* src1, uint64_t* dst1) {
-  __syncthreads();
-  copy_rows_of<kUnroll>(p.row_bytes0, src0, dst0, tn);
-  if (p.n_streams > 1) copy_rows_of<kUnroll>(p.row_bytes1, src1, dst1, tn);
+                               uint64_t* src1, uint64_t* dst1, bool deep) {
+  auto stream = [&](int64_t row_bytes, const uint64_t* src, const uint64_t* dst) {
+    if (deep) copy_rows_of<kUnroll>(row_bytes, src, dst, tn);
+    else copy_rows_of<kHostUnroll>(row_bytes, src, dst, tn);
+  };
+  stream(p.row_bytes0, src0, dst0);
+  if (p.n_streams > 1) stream(p.row_bytes1, src1, dst1);
   __syncthreads();
 }
 
