@@ -543,6 +543,7 @@ def _measure(spec, gather_mode, X, N, ptrs, ctx, warm, timed, dev):
                 raise RuntimeError(f"{spec.name}: the timed pass with events differs from the plain pass")
             stage_two = np.asarray(gather_ms, dtype=np.float64) + np.asarray(tail_ms, dtype=np.float64)
             res["match_ms"], res["stage_two_ms"] = np.asarray(match_ms, dtype=np.float64), stage_two
+            res["wall_events"] = wall
         else:
             res["wall"], res["delta"] = wall, d
     return res
@@ -602,7 +603,8 @@ def config_block(memcpy_peak, dev, warm=8, timed=32, with_cpu=True):
                     entry["hit_rate"] = round(d["hits"] / max(1, d["lookups"]), 5)
                     entry["misses_per_step"] = round(d["misses"] / timed, 1)
                     entry["host_rows_per_step"] = round(d["host_bytes"] / row_total / timed, 1)
-                    entry["match_frac_of_step"] = round(float(np.sum(m["match_ms"])) * 1e-3 / m["wall"], 4)
+                    # of the pass with events, whose steps are two launches (tiny's others are one)
+                    entry["match_frac_of_step"] = round(float(np.sum(m["match_ms"])) * 1e-3 / m["wall_events"], 4)
             if with_cpu:
                 us, threads = _oracle_us_per_step(spec, X_host, N_host, ptrs, warm, timed)
                 entry["cpu_oracle_us_per_step"] = round(us, 1)
@@ -1212,7 +1214,11 @@ def gather_host_bytes(d, row_total):
     """Host-link payload of the Stage Two kernels over a counter delta: all of
     it but the rows that the matching launch read into staging while Stage One
     ran (the early-fetch transfer, which has a list of early rows, reads its
-    staged rows in the launch that is timed)."""
+    staged rows in the launch that is timed).  The counter has every staged row,
+    so one that no miss took would be subtracted too; that needs an index whose
+    slot is forgotten between the table's read by the fetch and the same step's
+    write back, which the steps timed here, whose fetch reads the table some
+    10 us before that, do not show."""
     staged = 0 if d["early_rows"] else d["early_staged_rows"]
     return d["host_bytes"] - staged * row_total
 
