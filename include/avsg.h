@@ -78,8 +78,9 @@ typedef int32_t avsg_status;
                                    was lost to an exhausted probe chain or a bucket collision, so the probe of
                                    Eq. 8-11 cannot find it) is copied from that slot; a miss that repeats a
                                    miss of another token of the step (same index) is written by that index's
-                                   host copy, which fills up to two such repeats (further repeats, from four
-                                   tokens on, are copied from its slot).  Host rows go in 6-row tiles claimed
+                                   host copy, which fills up to two such repeats, or all three of a step
+                                   with four tokens (further ones are copied from its slot afterwards).  Host
+                                   rows go in tiles of up to 6 rows, the first ones dealt and the rest claimed
                                    by every CU.  Slots, counts, tables and buffer
                                    contents are identical to AVSG_GATHER_BALANCED.  Relies on the same
                                    property as a hit: a cached row below the verified length does not change
@@ -98,10 +99,10 @@ typedef int32_t avsg_status;
 
 #define AVSG_GATHER_AUTO 8      /* AVSG_GATHER_RESIDENT when a step looks up at least 8192 indices
                                    (B*N_q*K) with hash matching and the resident plan fits beside the
-                                   table, else AVSG_GATHER_BALANCED: below that size the plan costs more
-                                   than the host rows it saves (measured crossover between 4096 and 8192
-                                   lookups per step).  Resolved once, at create; avsg_resolve_config
-                                   tells which. */
+                                   table, else AVSG_GATHER_BALANCED: for few lookups the plan costs more
+                                   than the host rows it saves (measured crossover between 4096 and 12288
+                                   lookups per step by K and N_q).  Resolved once, at create;
+                                   avsg_resolve_config tells which. */
 
 #define AVSG_MAX_STREAMS 2
 
@@ -160,7 +161,11 @@ typedef struct avsg_stats_t {
     uint64_t early_rows;      /* AVSG_GATHER_EARLY: host rows fetched before Stage One (one per index) */
     uint64_t early_staged_rows;   /* of those, rows parked in staging until their slots were known;
                                      AVSG_GATHER_RESIDENT and _BALANCED: host rows read into staging
-                                     while Stage One ran (timing decides which, not what a step leaves) */
+                                     while Stage One ran (timing decides which, not what a step leaves).
+                                     A staged row that no miss takes is among them (an index hit in this
+                                     step and forgotten at its end, or one that the step's own slots,
+                                     written over its selections, seem to select); its link traffic is
+                                     in no byte counter */
     uint64_t early_deferred_rows; /* of those, rows read after Stage One because staging was full */
 } avsg_stats_t;
 
@@ -319,7 +324,9 @@ avsg_status avsg_export_misses(avsg_handle *h, int32_t r, int32_t *n_out, int32_
  *   n_rep, rep_src[k], rep_dst[k]  further repeats of an index missed by four
  *                                  or more tokens of the step: copied from the
  *                                  largest slot this step reserved for it, after
- *                                  the host copies.
+ *                                  the host copies.  With four tokens per step the
+ *                                  host copies write them too (unless the workspace
+ *                                  lacks its optional parts), and no copy follows.
  * Errors: AVSG_E_INVAL, AVSG_E_UNSUPPORTED (another gather mode), AVSG_E_HIP. */
 avsg_status avsg_export_plan(avsg_handle *h, int32_t r, int32_t *n_host, int32_t *host_x,
                              int32_t *host_o, int32_t *host_fan, int32_t *n_res, int32_t *res_src,
