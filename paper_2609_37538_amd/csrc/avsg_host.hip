@@ -369,9 +369,17 @@ avsg_status check_resolved(const avsg_config* c, std::string* why) {
 
 // AVSG_GATHER_AUTO: resident reuse when a step looks up at least this many
 // indices (B * N_q * K) and its plan fits beside the table, else the paper's
-// S3.  Measured crossover (µs per step, S3 / resident): 4096 lookups 33.5 / 35.4
-// (B = 2, K = 2048) and 40.6 / 43.8 (B = 1, two tokens); 8192 lookups 48.6 /
-// 44.7 (B = 4) and 55.1 / 52.8 (B = 2, two tokens).
+// S3.  One line for all sizes; where the two cross depends on K and N_q (µs per
+// step, S3 / resident, a tenth of the selections new in each step):
+//   lookups        4096          6144          8192          12288
+//   K = 256    13.5 / 17.2   16.9 / 19.5   20.0 / 21.6   26.7 / 25.5
+//   K = 512    13.5 / 16.0   16.8 / 16.6   20.6 / 18.6   28.1 / 21.9
+//   K = 1024   14.3 / 16.6   17.7 / 17.1   21.3 / 18.2   29.0 / 22.0
+//   K = 2048   16.5 / 19.3   19.8 / 19.5   24.3 / 20.0   32.8 / 23.2
+//   two tokens of K = 1024
+//              20.3 / 20.7   26.9 / 21.6   32.1 / 24.8   41.9 / 31.5
+//   four tokens of K = 1024
+//              20.5 / 25.8                 22.5 / 26.1
 constexpr long long kAutoResidentLookups = 8192;
 
 avsg_config resolved(const avsg_config& c) {

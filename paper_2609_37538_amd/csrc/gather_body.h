@@ -84,9 +84,12 @@ __device__ inline void request_prefix(const GatherParams& p, int* pre, int* wtot
 // r has nfirst(r) such workgroups; its n host entries go to them in tiles of
 // ceil(n / nfirst) rows, at least one and at most T0, so few entries still
 // spread over many CUs (one workgroup reads ~2.5 GB/s from the host).  No
-// request gets first tiles when one would get more than eight (ch > 8 B):
-// with 192 such workgroups, twelve per request (16 requests) made the step
-// slower than none, six (32 requests) and three (64) faster.
+// request gets first tiles when one would get more than eight (ch > 8 B): on 256
+// CUs that is below 16 requests, 192 of whose workgroups start with host rows
+// (128 from 16 on, eight each).  Step with them and without, us, one token, two
+// tokens: 12 requests 33.4 / 32.8, 88.9 / 89.7; 14 requests 36.5 / 36.2, 101.5 /
+// 103.0; 16 requests 39.2 / 40.0, 114.1 / 115.1; 24 requests 52.3 / 53.1, 164.3 /
+// 165.8; 48 requests 91.4 / 92.7, 316.6 / 318.4.
 __device__ __forceinline__ bool first_tiles_on(int B, int ch) { return ch <= 8 * B; }
 __device__ __forceinline__ int first_tiles(int r, int B, int ch) {
   return first_tiles_on(B, ch) && r < ch ? (ch - 1 - r) / B + 1 : 0;
