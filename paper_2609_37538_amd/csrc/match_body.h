@@ -291,8 +291,8 @@ __device__ __forceinline__ int plan_lookup(const uint32_t* smp, const int32_t* s
 // c[]; a word is (resident bit | early bit | tag | slot + 1), 0 = free, and
 // atomicMax makes every choice deterministic; beside it P fan words, one per
 // map word: the two largest repeat destinations of the word's index as two
-// 16-bit fields of slot + 1 (larger in the low field, 0 = none; a table holds
-// at most 2^14 slots), kept by a compare-and-swap loop, so the result does not
+// 15-bit fields of slot + 1 (larger in the low half, 0 = none; a table holds
+// at most 2^14 slots) and a bit for a further one, kept by a compare-and-swap loop, so the result does not
 // depend on the order of the bids.  A word's lowest bit marks that an index whose home is that word
 // sits further on (it may also be set on a word whose own index took a
 // larger slot; that only costs the scan below a probe).  The map holds at
