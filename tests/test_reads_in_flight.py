@@ -1,6 +1,6 @@
 """Reads in flight of the request- and position-level gathers: parity with the
-oracle on both sides of their rules, and all-miss steps as fast as the balanced
-gather's, which reads the same rows."""
+oracle on both sides of their rules, and steps as fast as the balanced gather's,
+which reads the same rows."""
 import numpy as np
 import pytest
 
@@ -38,11 +38,13 @@ def test_position_level_parity(workers, retention):
     run_parity(spec, gather_mode=4, gather_workers=workers, buffers_every=1, retry=1)
 
 
-@pytest.mark.parametrize("mode,batch,topk,slots,bound", [(4, 1, 2048, 8192, 1.05), (1, 400, 128, 256, 1.02)],
+@pytest.mark.parametrize("mode,batch,topk,slots,misses", [(4, 1, 2048, 8192, "all"), (1, 200, 512, 1024, "lost")],
                          ids=["position", "request"])
-def test_all_miss_steps_as_fast_as_balanced(mode, batch, topk, slots, bound):
-    """(With four reads per thread on 256 workgroups and more, the position
-    gather took 1.11 and the request gather 1.02 times as long.)"""
+def test_as_fast_as_balanced(mode, batch, topk, slots, misses):
+    """Position gather: a step of misses only; request gather: the same
+    selections in every step, of which those miss whose installs were lost.
+    (With four reads per thread on 256 and 200 workgroups they took 1.12 and
+    1.15 times as long as the balanced gather; they take 0.98 and 1.01.)"""
     from paper_2609_37538_amd import avsg as A
     import torch
     row_bytes = 1152
@@ -52,6 +54,8 @@ def test_all_miss_steps_as_fast_as_balanced(mode, batch, topk, slots, bound):
     rng = np.random.default_rng(4)
     order = np.stack([rng.permutation(rows) for _ in range(batch)]).astype(np.int32)
     X = [torch.from_numpy(np.ascontiguousarray(order[:, None, t * topk:(t + 1) * topk])).cuda() for t in range(12)]
+    if misses == "lost":
+        X = X[:1] * 12
     ops = [A.Operator(A.make_config(batch, topk, 1, slots, row_bytes=(row_bytes,), gather_mode=m), host, n_rows)
            for m in (0, mode)]
     if topk >= 512:   # the balanced one without room for rows staged during Stage One
@@ -73,9 +77,10 @@ def test_all_miss_steps_as_fast_as_balanced(mode, batch, topk, slots, bound):
                 end.record()
                 torch.cuda.synchronize()
                 best[i] = min(best[i], begin.elapsed_time(end) * 1e3 / 10)
-        log(f"[gpu] all misses, {batch} requests, mode {mode}: {best[1]:.1f} us per step, balanced {best[0]:.1f}")
-        assert ops[0].stats()["hits"] == 0 and ops[0].stats()["early_staged_rows"] == 0
-        assert best[1] < bound * best[0]
+        log(f"[gpu] {misses} misses, {batch} requests, mode {mode}: {best[1]:.1f} us per step, balanced {best[0]:.1f}")
+        st = ops[0].stats()
+        assert st["misses"] > 0 and (st["hits"] == 0) == (misses == "all") and st["early_staged_rows"] == 0
+        assert best[1] < 1.05 * best[0]
         assert all(torch.equal(a, b) for a, b in zip(ops[0].buffers, ops[1].buffers))
     finally:
         for op in ops:
